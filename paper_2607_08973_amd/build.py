@@ -42,10 +42,12 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found: ROCm is required to build libsifar")
 
 
-def build(verbose: bool = False) -> str:
-    """Compile every HIP/C++ source into libsifar.so (always recompiles)."""
-    tmp = LIB + ".tmp"
-    cmd = [hipcc(), *FLAGS, "-I", INCLUDE, "-I", CSRC, *SOURCES, "-o", tmp]
+def build(verbose: bool = False, lib: str = LIB, defines: tuple = ()) -> str:
+    """Compile every HIP/C++ source into libsifar.so (always recompiles), or
+    into `lib` with preprocessor `defines`."""
+    tmp = lib + ".tmp"
+    cmd = [hipcc(), *FLAGS, *[f"-D{d}" for d in defines], "-I", INCLUDE, "-I", CSRC, *SOURCES,
+           "-o", tmp]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, capture_output=True, text=True)
@@ -55,8 +57,8 @@ def build(verbose: bool = False) -> str:
         raise RuntimeError(f"hipcc failed ({res.returncode}):\n{out}")
     if verbose and out.strip():
         print(out, file=sys.stderr)
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, lib)
+    return lib
 
 
 if __name__ == "__main__":

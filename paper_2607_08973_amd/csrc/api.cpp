@@ -346,9 +346,10 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
     }
     h->exch_q = c.persistent && h->segs > h->groups_per_token ? h->segs : h->groups_per_token;
     if (c.persistent) {
-        // every consumer and producer wave of a step is resident at once
+        // every consumer and producer wave of a step is resident at once;
         // with the epilogue the grid pads the tokens to a multiple of 8 (one
-        // XCD per token)
+        // XCD per token). A plain grid's idle rows end at once and wait for
+        // nothing, so they take no place for long and are not counted.
         const int64_t tokens = c.epilogue ? 8 * ((static_cast<int64_t>(c.max_tokens) + 7) / 8)
                                           : c.max_tokens;
         const int64_t waves = 2 * tokens * h->segs;

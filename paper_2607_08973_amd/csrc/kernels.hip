@@ -1013,8 +1013,8 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
                    lane, wave);
 }
 
-// Grid (segs, tokens, 2) of one-wave workgroups, or with the epilogue
-// (8 * ceil(tokens / 8) * Q, 1, 2) of G-wave workgroups (G = 1, or
+// Grid (segs, plane_rows(tokens, segs), 2) of one-wave workgroups, or with the
+// epilogue (8 * ceil(tokens / 8) * Q, 1, 2) of G-wave workgroups (G = 1, or
 // kChainGroupWaves when GROUPED; Q = segs / G, layout below): plane 0 reduces
 // chunk (t, x * G + wave) for epochs base+1 .. base+L in order, plane 1
 // produces it. The last wave to arrive on the counter advances the epoch base
@@ -1258,7 +1258,7 @@ hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, 
     if (static_cast<uint64_t>(a.r.geo.nranks) * 4u * a.r.geo.slot_elems > 0x7fffffffull)
         return hipErrorInvalidValue;
     const dim3 grid = epilogue ? dim3(8u * t8 * q, 1, 2)
-                               : dim3(q, static_cast<uint32_t>(a.r.geo.tokens), 2);
+                               : dim3(q, static_cast<uint32_t>(plane_rows(a.r.geo.tokens, q)), 2);
     void *args[] = {const_cast<ChainArgs *>(&a)};
     return hipLaunchKernel(fn, grid, dim3(kLanes * waves), args, 0, s);
 }

@@ -41,6 +41,22 @@ __host__ __device__ inline uint32_t mod_u32(uint32_t x, const DivU32 &v) {
     return x - q * v.d;
 }
 
+// Token rows of a persistent plain step's planes: a plane of `tokens` rows of
+// `segs` one-wave workgroups, with rows of idle workgroups added until it is a
+// multiple of the 8 XCDs. Workgroups are dealt to the XCDs round robin, plane
+// 1 after plane 0, so a chunk's consumer and producer then share an XCD
+// whatever the shape. Without the added rows 45 chunks (N = 8, 5 tokens x
+// 4608) put every pair on two XCDs, which pays a release fence per epoch:
+// 162 us a 64-all-reduce step, 47 with them. (A macro, so that a test can build
+// the library with 1 and still run the cross-XCD handoffs.)
+#ifndef SIFAR_PLANE_ALIGN
+#define SIFAR_PLANE_ALIGN 8
+#endif
+inline int64_t plane_rows(int64_t tokens, int64_t segs) {
+    while (tokens * segs % SIFAR_PLANE_ALIGN != 0) ++tokens;
+    return tokens;
+}
+
 // Device-resident state shared by all kernels of a handle.
 struct DevState {
     uint32_t epoch_base;   // graph nodes compute g = epoch_base + node offset
@@ -150,7 +166,8 @@ int max_active_groups(int nranks, int mode, bool epilogue, int waves_per_group);
 // kChainGroupWaves); `prefetch` picks the one-wave kernel whose producer loads
 // an epoch's sources ahead (more registers, lower occupancy).
 int max_active_chain_groups(int nranks, int mode, bool epilogue, int waves, bool prefetch);
-// Persistent step: grid (segs / waves, tokens, 2); waves = 1, or
+// Persistent step: grid (segs, plane_rows(tokens, segs), 2), or with the
+// epilogue one that puts a token's workgroups on one XCD; waves = 1, or
 // kChainGroupWaves (segs divisible by it, waves * nranks <= 64) to let one
 // release fence cover a workgroup's chunks.
 hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, bool prefetch,
