@@ -12,8 +12,10 @@ One benchmark step = one decode step of 64 all-reduces for each of the four
 batch sizes: 256 all-reduces. By default (--persistent 1) a decode step is one
 persistent kernel launch whose consumer waves poll the stamps before they load
 the payload (ORDERED: no speculation) while producer waves play the peers
-concurrently; --persistent 0 replays a captured graph with one launch per
-all-reduce, whose reduction is the paper's speculative one (SPEC).
+concurrently; --persistent 0 runs the per-epoch step, whose reduction is the
+paper's speculative one (SPEC): one launch with a workgroup barrier between
+all-reduces (with the epilogue, one buffer, unfused peers or more than 4096
+chunks: a captured graph with one launch per all-reduce).
 
 Printed JSON line (rank 0):
   value            microseconds per all-reduce over the timed steps (HIP events
@@ -24,7 +26,7 @@ Printed JSON line (rank 0):
                    copies are reported apart) over its average launch period,
                    from HIP events on the launching stream; frac_cold the same
                    for steps run right after a 512 MiB scrub of the caches
-  spec_graph       the speculative per-launch chain on the same workload, with
+  spec_graph       the speculative per-epoch chain on the same workload, with
                    its own dominant kernel's fraction
   cpu_baseline     the CPU oracle on this host, on a bounded sample
 """
@@ -64,6 +66,15 @@ def produce_bytes(N: int, T: int, H: int) -> int:
     K = T * H * 2
     chunks = T * ((H + 511) // 512)
     return 2 * N * K + 4 * N * chunks
+
+
+def step_launches(L: int, chunks: int, persistent, fused, epilogue=False) -> int:
+    """Kernel launches of one decode step: one for a persistent step and for a
+    plain per-epoch step with the peers one epoch ahead whose chunks fit the
+    GPU as two-wave workgroups (16 on each of 256 CUs)."""
+    if persistent or (fused and not epilogue and chunks <= 4096):
+        return 1
+    return L + 2 if fused else 2 * L + 1
 
 
 def latency_floors() -> dict:
@@ -133,7 +144,7 @@ def graph_floor_us(nodes: int) -> float:
 
 TRAFFIC_PROFILES = {
     "persistent": os.path.join(ROOT, "profiles", "chain_llama8b_decode_n8_h4096.md"),
-    "fused": os.path.join(ROOT, "profiles", "fused_reduce_llama8b_decode_n8_h4096.md"),
+    "step": os.path.join(ROOT, "profiles", "step_llama8b_decode_n8_h4096.md"),
 }
 
 
@@ -179,12 +190,12 @@ def parse():
     ap.add_argument("--warmup", type=int, default=5)
     ap.add_argument("--mode", default=None, choices=["spec", "ordered", "none"],
                     help="validation; default: ordered for persistent steps (the only "
-                         "mode they accept), spec for one launch per all-reduce")
+                         "mode they accept), spec for per-epoch steps")
     ap.add_argument("--fuse", type=int, default=1, choices=[0, 1],
                     help="1: the peers' next write shares the reduction's launch")
     ap.add_argument("--persistent", type=int, default=1, choices=[0, 1],
                     help="1: one persistent launch per decode step (peers and reduction "
-                         "concurrent); 0: one launch per all-reduce")
+                         "concurrent); 0: the per-epoch step")
     ap.add_argument("--buffers", type=int, default=2, choices=[1, 2],
                     help="2: dual buffering; 1: one slot per rank (bottom barrier)")
     ap.add_argument("--floor-nodes", type=int, default=64)
@@ -198,7 +209,7 @@ def parse():
     ap.add_argument("--cpu-seconds", type=float, default=12.0,
                     help="budget of the CPU-oracle baseline (0 disables it)")
     ap.add_argument("--spec-graph", type=int, default=1,
-                    help="persistent runs: also time the speculative per-launch chain (1)")
+                    help="persistent runs: also time the speculative per-epoch chain (1)")
     ap.add_argument("--wide-points", type=int, default=1,
                     help="also time the chain at 16 and 64 tokens (1) or not (0: profiling "
                          "runs, whose averages cover the headline launches only)")
@@ -342,13 +353,13 @@ def chain_point(w, T, args, *, T_max=None, pool_entries=None, inject=False, wave
     out = {"workload": w.name, "nranks": N, "tokens": T, "hidden": H, "chain": L,
            "steps": args.steps, "us_per_reduce": ms * 1e3 / (args.steps * L)}
     fused_launch = args.fuse and args.buffers == 2
-    launches = 1 if args.persistent else (L + 2 if fused_launch else 2 * L + 1)
+    launches = step_launches(L, T * ((H + 511) // 512), args.persistent, fused_launch, w.epilogue)
     out["launch_period_us"] = ms * 1e3 / (args.steps * launches)
     red = reduce_bytes(N, T, H) + (epilogue_bytes(T, H) if w.epilogue else 0)
     out["reduce_bytes"] = red
     out["reduce_gbs"] = red / (out["us_per_reduce"] * 1e-6) / 1e9
     peers = produce_bytes(N, T, H) if (fused_launch or args.persistent) else 0
-    per_launch = L if args.persistent else 1
+    per_launch = L if launches == 1 else 1
     out["launch_bytes"] = red * per_launch
     out["launch_gbs"] = red * per_launch / (out["launch_period_us"] * 1e-6) / 1e9
     out["peer_copy_bytes_per_launch"] = peers * per_launch
@@ -405,7 +416,7 @@ def kernel_table(per_t, tokens, N, H, L, persistent, fused_launch):
     """Per batch size: the dominant kernel's launch period (from the HIP-event
     microseconds per all-reduce of a step), one consumer's algorithmic bytes
     per launch and the emulated peers' copy bytes per launch."""
-    if persistent:
+    if persistent:  # or any other step in one launch
         launches, per_launch = 1, L
     else:
         launches, per_launch = (L + 2 if fused_launch else 2 * L + 1), 1
@@ -421,13 +432,12 @@ def kernel_table(per_t, tokens, N, H, L, persistent, fused_launch):
 
 
 def spec_graph_point(w, pool, pool_d, args):
-    """The paper's speculative reduction on the headline workload: one
-    captured graph per decode step with one launch per all-reduce (the peers
-    of epoch g + 1 written by a second plane of the launch that reduces g),
-    payload and stamps loaded together, validated afterwards. Timed like the
-    headline (HIP events around the graph replays); its dominant kernel is the
-    fused reduction, L - 1 of a step's L + 2 launches. The last replay's
-    outputs are checked against the oracle."""
+    """The paper's speculative reduction on the headline workload: one launch
+    per decode step (the peers of epoch g + 1 written by a second wave of the
+    workgroup that reduces g, a workgroup barrier between epochs), payload and
+    stamps loaded together, validated afterwards. Timed like the headline (HIP
+    events around the steps); its dominant kernel is the step kernel. The last
+    step's outputs are checked against the oracle."""
     import numpy as np
     import torch
 
@@ -454,18 +464,18 @@ def spec_graph_point(w, pool, pool_d, args):
             assert np.array_equal(got[i, :T], oracle.reduce(pool[(g - 1) % pool.shape[0]][:, :T])), \
                 f"spec graph T={T} node {i}"
     s.close()
-    kern = kernel_table(per_t, tokens, N, H, L, False, True)
+    kern = kernel_table(per_t, tokens, N, H, L, True, True)
     period = sum(k["launch_period_us"] for k in kern.values()) / len(kern)
     byts = sum(k["bytes_per_launch"] for k in kern.values()) / len(kern)
     gbs = byts / (period * 1e-6) / 1e9
     return {"protocol": "SPEC: payload and stamps loaded together, validated after, retried "
-                        "on a stale stamp; one graph launch per all-reduce",
+                        "on a stale stamp; one launch per step, a workgroup barrier per all-reduce",
             "us_per_reduce": round(sum(per_t.values()) / len(per_t), 4),
             "us_per_reduce_by_tokens": {str(k): round(v, 4) for k, v in per_t.items()},
-            "dominant_kernel": "reduce_kernel<8, SPEC, no epilogue, fused peers>",
+            "dominant_kernel": "step_kernel<8, SPEC>",
             "launch_period_us": round(period, 4), "bytes_per_launch": round(byts),
             "achieved_gbs": round(gbs, 3), "frac": round(gbs / HBM_PEAK_GBS, 6),
-            "traffic": measured_traffic("fused")}
+            "traffic": measured_traffic("step")}
 
 
 def reduce_point(w, args, scrub, reps=30):
@@ -745,15 +755,16 @@ def main():
     floors = latency_floors()
 
     # ---- roofline of the dominant kernel -----------------------------------
-    # Persistent: one launch per step, L all-reduces in it. Per launch: with
-    # fused peers a step is produce(g1), L-1 launches of the fused
-    # reduce(g_i)+produce(g_i+1) kernel, reduce(g_L) and the epoch advance:
-    # the fused kernel is L-1 of the L+2 launches; its average launch period
-    # is the HIP-event step time over the launches of the step.
+    # Persistent steps, and per-epoch steps with the peers one epoch ahead:
+    # one launch per step, L all-reduces in it. One buffer or unfused peers: a
+    # producer and a reduction launch per all-reduce and the epoch advance; the
+    # average launch period is the HIP-event step time over the launches.
     # Algorithmic bytes are one consumer's share of each all-reduce (read
     # N*K, write K, read the stamps); the emulated peers' copies (read N*K,
     # write N*K, write the stamps) are reported apart.
-    kern = kernel_table(per_t, tokens, N, H, L, args.persistent, args.fuse and args.buffers == 2)
+    fused = args.fuse and args.buffers == 2
+    one = step_launches(L, max(tokens) * ((H + 511) // 512), args.persistent, fused) == 1
+    kern = kernel_table(per_t, tokens, N, H, L, one, fused)
     mean_period = sum(k["launch_period_us"] for k in kern.values()) / len(kern)
     mean_bytes = sum(k["bytes_per_launch"] for k in kern.values()) / len(kern)
     mean_peer = sum(k["peer_copy_bytes_per_launch"] for k in kern.values()) / len(kern)
@@ -776,15 +787,14 @@ def main():
             tot += a.elapsed_time(b) * 1e3
         cold_t[T] = tot / (reps * L)
     s.check()
-    kern_cold = kernel_table(cold_t, tokens, N, H, L, args.persistent,
-                             args.fuse and args.buffers == 2)
+    kern_cold = kernel_table(cold_t, tokens, N, H, L, one, fused)
     cold_period = sum(k["launch_period_us"] for k in kern_cold.values()) / len(kern_cold)
     achieved_cold = mean_bytes / (cold_period * 1e-6) / 1e9
     del scrub
     graph_next_epoch, _ = s.epochs()   # the ring now holds the last step at T = tokens[-1]
     graph_ring = ring.cpu().numpy().view(np.uint16).copy()
 
-    # ---- the speculative per-launch chain (the paper's SPEC) --------------
+    # ---- the speculative per-epoch chain (the paper's SPEC) ---------------
     spec = None
     if args.persistent and args.spec_graph:
         spec = spec_graph_point(w, pool, pool_d, args)
@@ -810,7 +820,7 @@ def main():
     if args.mode == "ordered" and args.buffers == 2 and args.persistent:
         traffic = measured_traffic("persistent")
     elif args.mode == "spec" and args.buffers == 2 and args.fuse:
-        traffic = measured_traffic("fused")
+        traffic = measured_traffic("step")
 
     cpu = None
     if args.cpu_seconds > 0:
@@ -853,10 +863,11 @@ def main():
                    "protocol": ("ORDERED: stamps polled before the payload is loaded (no "
                                 "speculation), peers concurrent in one persistent launch"
                                 if args.persistent else
-                                f"{args.mode.upper()} in one launch per all-reduce"),
+                                f"{args.mode.upper()}, " + ("a workgroup barrier" if one else
+                                                            "a launch") + " per all-reduce"),
                    "persistent": args.persistent, "buffers": args.buffers,
-                   "step": (f"{len(tokens)} decode steps of {L} all-reduces, one persistent "
-                            f"launch each" if args.persistent else
+                   "step": (f"{len(tokens)} decode steps of {L} all-reduces, one "
+                            f"{'persistent ' if args.persistent else ''}launch each" if one else
                             f"{len(tokens)} captured decode-step graphs of {L} all-reduces")},
         "reduces_per_s": round(1e6 / us_per_reduce, 1),
         "us_per_reduce_by_tokens": {str(k): round(v, 4) for k, v in per_t.items()},

@@ -78,8 +78,9 @@ typedef struct sifar_ctx *sifar_t;
  *          re-runs both. Correct when a rank whose stamp is fresh at
  *          validation also had its payload in place when it was loaded -- the
  *          monotonicity assumption of Sec. 8.1. It holds for the per-epoch
- *          launches (eager calls, step graphs with persistent = 0): every
- *          epoch's payload was written by an earlier launch. It does not hold
+ *          launches (eager calls, steps with persistent = 0): every epoch's
+ *          payload was written by an earlier launch, or before the workgroup
+ *          barrier that starts the reduction's phase. It does not hold
  *          for a producer that is writing at that moment: measured on MI355X
  *          with producer and consumer on different XCDs, ~2 % of persistent
  *          all-reduces accepted a rank's previous epoch under a fresh stamp
@@ -135,9 +136,9 @@ typedef struct {
     uint32_t spin_limit;      /* bound on the epilogue's cross-segment wait, in polls, >= 1 */
     int32_t log_epochs;       /* decision-log ring length, in epochs, >= 1 */
     int32_t waves_per_group;  /* waves (64 lanes) per workgroup: 1, 2, 4, 8 or 16 */
-    int32_t fuse_peers;       /* step graphs: 1 = the launch reducing epoch g also writes the
-                                 peers' epoch g + 1 (other parity); 0 = separate producer and
-                                 reduction launches */
+    int32_t fuse_peers;       /* per-epoch steps: 1 = while epoch g is reduced the peers write
+                                 epoch g + 1 (other parity), see sifar_step; 0 = separate
+                                 producer and reduction launches */
     int32_t persistent;       /* step graphs: 1 = one persistent launch runs the whole step, its
                                  consumer waves and the emulated peers' waves synchronising
                                  through stamps in flight (a megakernel-style chain, Sec. 5);
@@ -227,10 +228,15 @@ typedef struct {
 int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
 
 /* Enqueue one decode step for `tokens` tokens: L all-reduces plus one
- * epoch-counter advance. Per-epoch steps are one hipGraphLaunch: with
- * fuse_peers the graph is produce(g1), then L-1 launches that each reduce g_i
- * while writing g_(i+1), then reduce(g_L): L + 1 kernel nodes; without it,
- * L x (produce, reduce). A persistent step is one kernel launch for the whole
+ * epoch-counter advance. A per-epoch step with fuse_peers runs in phases:
+ * produce(g1), then L-1 phases that each reduce g_i while the peers write
+ * g_(i+1), then reduce(g_L). A plain one whose chunks all fit the GPU at once
+ * as two-wave workgroups (4096 chunks on MI355X) is one kernel launch: a
+ * workgroup is one chunk, its first wave the reduction, its second the peers,
+ * and a workgroup barrier separates the phases. Any other is one
+ * hipGraphLaunch of a kernel node per phase (L + 1); without fuse_peers, of
+ * L x (produce, reduce). Outputs, logs and errors are the same either way.
+ * A persistent step is one kernel launch for the whole
  * step (a one-node graph replay measured slower). In a persistent step the
  * peers run concurrently with the reduction, so a reduction often reaches an
  * epoch before its stamps (the decision log records the polls: attempts and

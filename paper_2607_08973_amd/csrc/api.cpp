@@ -20,6 +20,7 @@ struct sifar_ctx {
     int groups_per_token = 1;
     bool chain_grouping = false;  // persistent steps may use kChainGroupWaves-wave workgroups
     bool chain_prefetch = false;  // one-wave persistent steps' producers load sources ahead
+    int step_cap = 0;             // workgroups of a one-launch per-epoch step that fit at once
     uint64_t slot_elems = 0;
 
     uint16_t *slots = nullptr;     // [N][2][slot_elems]
@@ -199,8 +200,10 @@ int chain_args(const sifar_t h, int32_t tokens, ChainArgs *ca) {
     ca->r = reduce_args(h, tokens, ep);
     // a persistent step's late ranks write their payload on time and delay
     // only their stamps (late_delay): nothing is staged
-    ca->p.stage = nullptr;
-    ca->r.stage = nullptr;
+    if (h->cfg.persistent) {
+        ca->p.stage = nullptr;
+        ca->r.stage = nullptr;
+    }
     if (h->cfg.epilogue) {
         ca->r.residual = static_cast<uint16_t *>(h->buf.residual);
         ca->r.weight = static_cast<const uint16_t *>(h->buf.weight);
@@ -272,6 +275,16 @@ int capture_step(sifar_t h, int32_t tokens, hipGraphExec_t *out) {
         rc = SIFAR_EHIP;
     if (graph) (void)hipGraphDestroy(graph);
     return rc;
+}
+
+// Epoch accounting of a step enqueued from `base`.
+void step_enqueued(sifar_t h, int32_t tokens, uint32_t base) {
+    const uint32_t L = static_cast<uint32_t>(h->cfg.reduces_per_step);
+    h->base_host = base + L + (L & 1u);
+    h->next_prod = h->next_red = base + L + 1;
+    const uint32_t last = h->next_red - 1;
+    h->prod_tokens[last & 1u] = tokens;
+    h->prod_tokens[(last + 1) & 1u] = tokens;
 }
 
 }  // namespace
@@ -370,6 +383,9 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
         h->chain_grouping = c.nranks * kChainGroupWaves <= kLanes && gcap > 0 &&
                             waves / kChainGroupWaves <= gcap;
     }
+    if (!c.persistent && !c.epilogue && c.fuse_peers && c.buffers == 2 &&
+        step_offsets_fit(c.nranks, h->slot_elems))
+        h->step_cap = max_active_step_groups(c.nranks, c.validate);
     rc = SIFAR_OK;
     if (!rc) rc = dev_alloc(&h->slots, static_cast<size_t>(c.nranks) * 2 * h->slot_elems);
     if (!rc) rc = dev_alloc(&h->stamps, static_cast<size_t>(2) * h->w_max * c.nranks);
@@ -525,7 +541,6 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
     if (tokens < 1 || tokens > h->cfg.max_tokens) return SIFAR_EINVAL;
     if (h->next_prod != h->next_red) return SIFAR_ESTATE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int L = h->cfg.reduces_per_step;
     // Graph nodes take parity (i + 1) & 1 for epoch base + i + 1: base must be even.
     uint32_t base = h->next_red - 1;
     base += base & 1u;
@@ -541,11 +556,21 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
         rc = hip_status(
             launch_chain(ca, h->cfg.validate, h->cfg.epilogue != 0, waves, h->chain_prefetch, s));
         if (rc) return rc;
-        h->base_host = base + static_cast<uint32_t>(L + (L & 1));
-        h->next_prod = h->next_red = base + static_cast<uint32_t>(L) + 1;
-        const uint32_t last = h->next_red - 1;
-        h->prod_tokens[last & 1u] = tokens;
-        h->prod_tokens[(last + 1) & 1u] = tokens;
+        step_enqueued(h, tokens, base);
+        return SIFAR_OK;
+    }
+    // A per-epoch step in one launch wherever its workgroups fit at once (the
+    // kernel's comment has both sides measured).
+    if (static_cast<int64_t>(tokens) * h->segs <= h->step_cap) {
+        if (base != h->base_host) {
+            rc = hip_status(launch_set_base(&h->state->epoch_base, base, s));
+            if (rc) return rc;
+        }
+        ChainArgs ca{};
+        chain_args(h, tokens, &ca);
+        rc = hip_status(launch_step(ca, h->cfg.validate, s));
+        if (rc) return rc;
+        step_enqueued(h, tokens, base);
         return SIFAR_OK;
     }
     auto it = h->graphs.find(tokens);
@@ -563,11 +588,7 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
         h->base_host = base;
     }
     if (hipGraphLaunch(exec, s) != hipSuccess) return SIFAR_EHIP;
-    h->base_host = base + static_cast<uint32_t>(L + (L & 1));
-    h->next_prod = h->next_red = base + static_cast<uint32_t>(L) + 1;
-    const uint32_t last = h->next_red - 1;
-    h->prod_tokens[last & 1u] = tokens;
-    h->prod_tokens[(last + 1) & 1u] = tokens;
+    step_enqueued(h, tokens, base);
     return SIFAR_OK;
 }
 

@@ -7,9 +7,11 @@
 // no wave waits for another during the reduction proper.
 //
 // Two ways to run a decode step:
-//  - per-epoch launches (eager calls, step graphs): the producer of an epoch
-//    always finishes in an earlier launch than the reduction of that epoch, so
-//    the paper's speculative reduction (SPEC) is exact here;
+//  - per-epoch phases: the producer of an epoch always finishes before the
+//    reduction of that epoch starts, so the paper's speculative reduction
+//    (SPEC) is exact here. Eager calls and step graphs put a launch boundary
+//    between the two, step_kernel (a whole step in one launch) a workgroup
+//    barrier;
 //  - one persistent launch per step (chain_kernel): consumer and producer
 //    waves run concurrently and synchronise through stamps and per-chunk
 //    consumed/produced words; the consumer validates before it loads
@@ -1061,6 +1063,197 @@ __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
     }
 }
 
+// ---------------------------------------------------------------------------
+// Per-epoch step in one launch: every all-reduce of a decode step, with a
+// workgroup barrier where the step graph has a launch boundary.
+//
+// A workgroup is one chunk: wave 0 is its consumer, wave 1 plays its peers.
+// Phase i: the peers write epoch base + i + 1 while the consumer reduces epoch
+// base + i; the barrier between phases orders them as the end of a launch
+// would, so speculation is as exact here as there: whatever the consumer loads
+// in a phase was written before the barrier. Chunks share nothing, so no
+// workgroup waits for another. Barrier and loads stay on one CU: the peers'
+// stores need no acknowledgement and no release fence before the barrier, the
+// consumer's loads follow them through the CU's memory pipeline and are served
+// by the XCD's L2 (agent scope: past the L1).
+//
+// What bounds it: the consumer's phase, one L2 round trip (payload and stamps
+// together), the rest of the sum that the loads' arrival does not cover, and
+// the issue of its stores; from 1024 chunks at N = 8 the bytes. Measured
+// against one launch per all-reduce (us per all-reduce, launches -> one
+// launch): N = 8, 4 tokens x 4096, 64 per step, 2.62 -> 0.62; with 10 % late
+// stamps 3.70 -> 1.28; 20 per step: N = 2, 1 x 4096, 2.59 -> 0.49; N = 8, 64 x
+// 4096, 3.69 -> 1.14; 64 x 8192, 5.49 -> 3.04; 256 x 8192 (4096 chunks, every
+// wave slot of the GPU), 16.3 -> 14.0; N = 2, 256 x 8192, 6.46 -> 3.92. It is
+// the faster one wherever its workgroups fit at once, so that is the rule;
+// beyond that, chunks would run their whole step one after another, which no
+// sequence of all-reduces does.
+
+// Phase boundary: orders the two waves' memory operations on their CU.
+__device__ __forceinline__ void phase_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// The peers of one chunk. `done` (LDS): the last epoch of each parity that the
+// consumer of this launch has finished; the first epoch of each parity checks
+// the words that earlier launches left in memory.
+template <int N>
+__device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base, const Chunk &k,
+                                              int lane, uint32_t (&done)[2]) {
+    const ProduceArgs &a = A.p;
+    const Geometry &geo = a.geo;
+    V16 v[N];
+    load_sources<N>(a, k, base + 1u, v);
+    for (int i = 0; i < A.reduces; ++i) {
+        const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
+        const uint32_t p = static_cast<uint32_t>(i + 1) & 1u;
+        const size_t pc = static_cast<size_t>(p) * geo.w_max + k.c;
+        // Dual-buffer rule: the slot's previous epoch must have been consumed.
+        uint32_t prev = g - 2u, fin;
+        if (i < 2) {
+            prev = ld_relaxed(a.produced + pc);
+            fin = ld_relaxed(a.consumed + pc);
+        } else {
+            fin = __hip_atomic_load(&done[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        const uint32_t inj = inject_word(a.inject, a.inject_div, g);
+        if (a.stage && late_ranks(inj)) {
+            const uint32_t staged = late_ranks(inj);
+            const uint64_t at = static_cast<uint64_t>(p) * geo.slot_elems + k.row;
+            if (k.lane_ok) {
+#pragma unroll
+                for (int r = 0; r < N; ++r)
+                    st16((((staged >> r) & 1u) ? a.stage : a.slots) + at + r * 2 * geo.slot_elems,
+                         v[r]);
+            }
+        } else {
+            store_slots_at<N>(a, k, p, v);
+        }
+        if (lane == 0 && prev != fin) latch(a.err, kErrWaw, g, k.c, prev);
+        // the stamps follow the payload
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane < N && !((held_back(inj) >> lane) & 1u)) st_flag(a.stamps + pc * N + lane, g, true);
+        if (lane == 0) st_flag(a.produced + pc, g, true);
+        // the next epoch's sources travel while the consumer works
+        if (i + 1 < A.reduces) load_sources<N>(a, k, g + 1u, v);
+        phase_barrier();
+    }
+}
+
+// Moves the late ranks' payload of a chunk from the stage into the slots, then
+// their stamps: the ranks catch up.
+template <int N>
+__device__ __forceinline__ void catch_up(const ReduceArgs &a, const Chunk &k, uint32_t g,
+                                         uint32_t p, int lane, uint32_t *stamp) {
+    const uint32_t late = late_ranks(inject_word(a.inject, a.inject_div, g));
+    const uint64_t rank_step = 2 * a.geo.slot_elems;
+    const uint64_t at = static_cast<uint64_t>(p) * a.geo.slot_elems + k.row;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        if ((late >> r) & 1u) {
+            const V16 x = ld16(a.stage + at + r * rank_step);
+            if (k.lane_ok) st16(a.slots + at + r * rank_step, x);
+        }
+    }
+    // the payload is published before the stamps, as a peer would; both are
+    // read again by this wave alone
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (lane < N && ((late >> lane) & 1u)) st_flag(stamp + lane, g, true);
+}
+
+template <int N, int MODE>
+__device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base, const Chunk &k,
+                                              int lane, uint32_t (&done)[2]) {
+    const ReduceArgs &a = A.r;
+    const Geometry &geo = a.geo;
+    const uint32_t off = lane_offset(geo, k);
+    const uint32_t rank_bytes = static_cast<uint32_t>(geo.slot_elems) * 4u;
+    for (int i = 0; i < A.reduces; ++i) {
+        const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
+        const uint32_t p = static_cast<uint32_t>(i + 1) & 1u;
+        const size_t pc = static_cast<size_t>(p) * geo.w_max + k.c;
+        const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(
+            a.slots + static_cast<uint64_t>(p) * geo.slot_elems + chunk_first(geo, k));
+        uint32_t *stamp = a.stamps + pc * N;
+        const uint32_t *stamp_lane = stamp + (lane < N ? lane : N - 1);
+        auto load = [&](V16(&v)[N]) {
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+                v[r] = ld16_agent_at(rs, off, static_cast<uint32_t>(r) * rank_bytes);
+        };
+        phase_barrier();
+        V16 v[N];
+        uint32_t st = 0, attempts = 1, first = 0, last = 0;
+        if (MODE != kOrdered) load(v);
+        if (MODE != kNone) st = ld_relaxed(stamp_lane);
+        // speculative: the sum runs as the payload arrives, the stamps decide
+        // afterwards whether it stands
+        V16 o;
+        if (MODE != kOrdered) o = sum_round<N>(v);
+        const uint32_t st_first = st;
+        if (MODE != kNone) {
+            uint32_t m = static_cast<uint32_t>(__ballot(lane < N && st != g));
+            first = last = m;
+            bool fail = m != 0 || a.forced_retries >= 1;
+            while (fail) {
+                if (attempts >= a.max_attempts) {
+                    if (lane == 0) latch(a.err, kErrRetryBudget, g, k.c, attempts);
+                    break;
+                }
+                if (attempts == 1 && a.stage && m != 0) catch_up<N>(a, k, g, p, lane, stamp);
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if (MODE != kOrdered) load(v);
+                st = ld_relaxed(stamp_lane);
+                ++attempts;
+                m = static_cast<uint32_t>(__ballot(lane < N && st != g));
+                last = m;
+                fail = m != 0 || attempts <= a.forced_retries;
+                if (MODE != kOrdered && !fail) o = sum_round<N>(v);
+            }
+        }
+        if (MODE == kOrdered) {
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            load(v);
+            o = sum_round<N>(v);
+        }
+        complete(o);  // every payload load has returned: the slot is free
+        if (lane == 0)
+            __hip_atomic_store(&done[p], g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        write_log(a, k, g, log_word(attempts, first, last));
+        write_stamp_log<N>(a, k, g, lane < N ? lane : N - 1, st_first, st);
+        st_flag(a.consumed + pc, g, true);
+        // lanes past the row's end store the owning lane's bytes again
+        st16_stream(a.out + static_cast<uint64_t>(i) * A.ring_stride + k.row, o);
+    }
+}
+
+// Grid (segs, tokens), two waves. The last workgroup to arrive on the counter
+// advances the epoch base for the next step: both waves of every workgroup
+// read it before their first barrier.
+template <int N, int MODE>
+__global__ __launch_bounds__(2 * kLanes, 8) void step_kernel(ChainArgs A) {
+    __shared__ uint32_t done[2];
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kLanes);
+    const uint32_t base = A.r.ep.base[0];
+    const Chunk k = chunk_at(A.r.geo, blockIdx.y, blockIdx.x, lane);
+    if (wave == 1) {
+        step_producer<N>(A, base, k, lane, done);
+        return;
+    }
+    step_consumer<N, MODE>(A, base, k, lane, done);
+    if (lane == 0) {
+        const uint32_t before =
+            __hip_atomic_fetch_add(A.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (before == gridDim.x * gridDim.y - 1u) {
+            st_relaxed(A.done, 0u);
+            st_relaxed(A.epoch_base, base + A.advance);
+        }
+    }
+}
+
 __global__ void advance_kernel(uint32_t *base, uint32_t step) {
     if (threadIdx.x == 0) base[0] += step;
 }
@@ -1155,6 +1348,30 @@ const void *chain_fn_any(int nranks, int mode, bool epi, bool grouped, bool pref
         case 6: return chain_fn_n<6>(mode, epi, grouped, prefetch);
         case 7: return chain_fn_n<7>(mode, epi, grouped, prefetch);
         case 8: return chain_fn_n<8>(mode, epi, grouped, prefetch);
+    }
+    return nullptr;
+}
+
+template <int N>
+const void *step_fn_n(int mode) {
+    switch (mode) {
+        case kSpec: return reinterpret_cast<const void *>(step_kernel<N, kSpec>);
+        case kOrdered: return reinterpret_cast<const void *>(step_kernel<N, kOrdered>);
+        case kNone: return reinterpret_cast<const void *>(step_kernel<N, kNone>);
+    }
+    return nullptr;
+}
+
+const void *step_fn_any(int nranks, int mode) {
+    switch (nranks) {
+        case 1: return step_fn_n<1>(mode);
+        case 2: return step_fn_n<2>(mode);
+        case 3: return step_fn_n<3>(mode);
+        case 4: return step_fn_n<4>(mode);
+        case 5: return step_fn_n<5>(mode);
+        case 6: return step_fn_n<6>(mode);
+        case 7: return step_fn_n<7>(mode);
+        case 8: return step_fn_n<8>(mode);
     }
     return nullptr;
 }
@@ -1255,12 +1472,25 @@ hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, 
     // the slots are addressed at 32-bit offsets from rank 0's (payload loads,
     // slot stores); co-residency keeps a step far below that (at most 4096
     // chunks: under 64 MiB of slots)
-    if (static_cast<uint64_t>(a.r.geo.nranks) * 4u * a.r.geo.slot_elems > 0x7fffffffull)
-        return hipErrorInvalidValue;
+    if (!step_offsets_fit(a.r.geo.nranks, a.r.geo.slot_elems)) return hipErrorInvalidValue;
     const dim3 grid = epilogue ? dim3(8u * t8 * q, 1, 2)
                                : dim3(q, static_cast<uint32_t>(plane_rows(a.r.geo.tokens, q)), 2);
     void *args[] = {const_cast<ChainArgs *>(&a)};
     return hipLaunchKernel(fn, grid, dim3(kLanes * waves), args, 0, s);
+}
+
+hipError_t launch_step(const ChainArgs &a, int mode, hipStream_t s) {
+    const void *fn = step_fn_any(a.r.geo.nranks, mode);
+    if (!fn || a.parity_mask != 1u || !a.r.stamp_log) return hipErrorInvalidValue;
+    // the slots are addressed at 32-bit offsets from rank 0's
+    if (!step_offsets_fit(a.r.geo.nranks, a.r.geo.slot_elems)) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<uint32_t>(a.r.geo.segs), static_cast<uint32_t>(a.r.geo.tokens));
+    void *args[] = {const_cast<ChainArgs *>(&a)};
+    return hipLaunchKernel(fn, grid, dim3(2 * kLanes), args, 0, s);
+}
+
+int max_active_step_groups(int nranks, int mode) {
+    return resident_groups(step_fn_any(nranks, mode), 2 * kLanes);
 }
 
 int max_active_groups(int nranks, int mode, bool epilogue, int waves_per_group) {

@@ -172,6 +172,14 @@ int max_active_chain_groups(int nranks, int mode, bool epilogue, int waves, bool
 // release fence cover a workgroup's chunks.
 hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, bool prefetch,
                         hipStream_t s);
+// One-launch steps address the slots at 32-bit offsets from rank 0's.
+inline bool step_offsets_fit(int nranks, uint64_t slot_elems) {
+    return static_cast<uint64_t>(nranks) * 4u * slot_elems <= 0x7fffffffull;
+}
+// Per-epoch step in one launch (plain, dual buffers): grid (segs, tokens) of
+// two-wave workgroups, and how many of them can be resident at once.
+hipError_t launch_step(const ChainArgs &a, int mode, hipStream_t s);
+int max_active_step_groups(int nranks, int mode);
 hipError_t launch_advance(uint32_t *epoch_base, uint32_t step, hipStream_t s);
 hipError_t launch_set_base(uint32_t *epoch_base, uint32_t value, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, uint64_t count, hipStream_t s);

@@ -1,0 +1,122 @@
+"""Per-epoch steps in one launch (plain, dual buffers, peers one epoch ahead)
+against the same steps as separate producer and reduction launches
+(fuse_peers = 0) and the oracle: outputs, decision log and raw stamps must be
+the same words, whatever the shape, validation mode, chain length, injected
+late ranks, forced retries or waves per workgroup of the launches."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from sifar_harness import StepRun, inject_table, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True, scope="module")
+def _gpu():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+
+
+def _same_words(a, b, T, epochs):
+    segs = a.s.log_geometry()[1]
+    rows = [(g - 1) % a.L for g in epochs]
+    la, lb = a.s.read_log()[rows, :T * segs], b.s.read_log()[rows, :T * segs]
+    assert np.array_equal(la, lb), "decision logs"
+    w = a.T_max * segs
+    sa = a.s.read_stamp_log().reshape(a.L, w, 2, a.N)[rows, :T * segs]
+    sb = b.s.read_stamp_log().reshape(b.L, w, 2, b.N)[rows, :T * segs]
+    assert np.array_equal(sa, sb), "stamp logs"
+
+
+# the smallest row, a row of one full and one 8-element chunk, ragged rows,
+# many chunks; chain lengths of 1, 2 and odd; every rank count's ends
+@pytest.mark.parametrize("mode", ["spec", "ordered", "none"])
+@pytest.mark.parametrize("N,T,H,L,G", [(1, 1, 8, 1, 1), (8, 3, 520, 2, 2), (5, 7, 3896, 5, 16),
+                                       (2, 9, 4608, 7, 4), (8, 64, 4096, 4, 1),
+                                       (3, 130, 8192, 3, 8)])
+def test_one_launch_equals_separate_launches(N, T, H, L, G, mode):
+    w = synth.Workload(82, f"one-launch-{N}-{T}-{H}", N, (T,), H, L, 1, "act")
+    a = StepRun(w, T, validate=mode, fuse_peers=1)
+    b = StepRun(w, T, validate=mode, fuse_peers=0, waves_per_group=G, pool=a.pool)
+    for tokens in (T, max(1, T // 2), T):
+        print(f"one launch N={N} T={tokens} H={H} L={L} {mode}", flush=True)
+        ea, eb = a.step(tokens), b.step(tokens)
+        assert ea == eb
+        got = to_host(a.out_d)
+        exp = oracle.reduce_chain(a.pool, ea, tokens)
+        for i in range(L):
+            assert np.array_equal(got[i, :tokens], exp[i]), f"tokens={tokens} node={i}"
+        _same_words(a, b, tokens, ea)
+    for r in (a, b):
+        r.s.check()
+        r.s.close()
+
+
+@pytest.mark.parametrize("mode", ["spec", "ordered"])
+@pytest.mark.parametrize("N,T,H,forced", [(8, 2, 4096, 0), (3, 3, 1000, 2), (8, 1, 520, 1)])
+def test_late_ranks_catch_up_the_same(N, T, H, forced, mode):
+    L = 12
+    w = synth.Workload(83, f"one-launch-late-{N}-{H}", N, (T,), H, L, 1, "act")
+    late = synth.delay_table(83, N, 2 * L + 1, 0.3)
+    a = StepRun(w, T, validate=mode, forced_retries=forced, fuse_peers=1)
+    b = StepRun(w, T, validate=mode, forced_retries=forced, fuse_peers=0, pool=a.pool)
+    for r in (a, b):
+        r.s.set_injection(inject_table(late))
+    for step in range(4):
+        print(f"late ranks N={N} T={T} H={H} forced={forced} {mode} step {step}", flush=True)
+        ea, eb = a.step(T), b.step(T)
+        assert ea == eb
+        got = to_host(a.out_d)
+        exp = oracle.reduce_chain(a.pool, ea, T)
+        for i in range(L):
+            assert np.array_equal(got[i, :T], exp[i]), f"step={step} node={i}"
+        _same_words(a, b, T, ea)
+    for r in (a, b):
+        r.s.check()
+        r.s.close()
+
+
+def test_batches_on_both_sides_of_the_launch_rule():
+    """4096 chunks fill the GPU with two-wave workgroups: steps of up to 256
+    tokens x 8192 are one launch, the next is a graph of launches. One handle
+    crosses the line both ways and its epochs go on."""
+    N, H, L, T_max = 2, 8192, 3, 258
+    w = synth.Workload(84, "one-launch-or-graph", N, (T_max,), H, L, 1, "uniform")
+    pool = synth.payload_pool(84, N, T_max, H, 4, "uniform")
+    r = StepRun(w, T_max, pool=pool)
+    for tokens in (256, 257, 1, 258, 255):
+        print(f"launch rule T={tokens}", flush=True)
+        epochs = r.step(tokens)
+        got = to_host(r.out_d)
+        exp = oracle.reduce_chain(pool, epochs, tokens)
+        for i in range(L):
+            assert np.array_equal(got[i, :tokens], exp[i]), f"tokens={tokens} node={i}"
+    # an eager epoch between steps (odd epoch counts, so the base is set anew)
+    out = torch.zeros((257, H), dtype=torch.int16, device=r.pool_d.device)
+    r.s.produce(r.pool_d[1], 257)
+    r.s.reduce(out, 257)
+    assert np.array_equal(to_host(out), oracle.reduce(pool[1][:, :257]))
+    epochs = r.step(5)
+    exp = oracle.reduce_chain(pool, epochs, 5)
+    got = to_host(r.out_d)
+    for i in range(L):
+        assert np.array_equal(got[i, :5], exp[i]), f"after an eager epoch, node={i}"
+    r.s.check()
+    r.s.close()
+
+
+def test_withheld_stamp_in_one_launch_latches():
+    w = synth.Workload(85, "one-launch-withheld", 8, (2,), 1024, 6, 1, "normal")
+    r = StepRun(w, 2, max_attempts=7)
+    r.s.set_injection(inject_table(np.zeros(6), withheld=np.array([0, 0, 4, 0, 0, 0])))
+    r.step(2)
+    assert r.s.status() == -5
+    kind, epoch, chunk, attempts = r.s.error_info()
+    assert (kind, epoch, attempts) == (1, 3, 7) and chunk < 4
+    log = r.s.read_log()[2, :4]
+    assert np.all((log & 0xFFFF) == 7) and np.all((log >> 24) == 4)
+    r.s.close()
