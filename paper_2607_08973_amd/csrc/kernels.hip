@@ -39,6 +39,8 @@
 #include "coherence.h"
 #include "sifar_kernels.h"
 
+#include <type_traits>
+
 namespace sifar {
 namespace {
 
@@ -471,6 +473,39 @@ __device__ __forceinline__ void write_stamp_log(const ReduceArgs &a, const Chunk
     row[N] = last;
 }
 
+// Sum over the wave, the bit-identical total in every lane: the butterfly over
+// lane distances 32, 16, 8, 4, 2, 1. The first two steps exchange half-waves
+// and rows with gfx950's lane swaps; within a row of 16 a rotation by 8, 4, 2
+// or 1 reaches a lane that holds the same value as the butterfly's partner
+// (lanes that differ only in the bits already summed hold equal values). All
+// of it stays in vector registers. A persistent epilogue step (N = 8, 8 x 8192,
+// 20 all-reduces) ran at 2.33 us per all-reduce with LDS-crossbar shuffles
+// here and in lanes_sum and the residual re-read every epoch; 1.67 with this
+// and lane reads in lanes_sum, 1.34 with both as they are.
+__device__ __forceinline__ float wave_sum(float v) {
+    auto pair = [](auto r) { return __uint_as_float(r[0]) + __uint_as_float(r[1]); };
+    const auto bits = [](float x) { return __float_as_uint(x); };
+    v = pair(__builtin_amdgcn_permlane32_swap(bits(v), bits(v), false, false));
+    v = pair(__builtin_amdgcn_permlane16_swap(bits(v), bits(v), false, false));
+    auto ror = [&](auto ctrl) {
+        const int x = static_cast<int>(bits(v));
+        v = v + __uint_as_float(static_cast<uint32_t>(
+                    __builtin_amdgcn_update_dpp(x, x, decltype(ctrl)::value, 0xF, 0xF, true)));
+    };
+    ror(std::integral_constant<int, 0x128>{});  // row_ror:8
+    ror(std::integral_constant<int, 0x124>{});
+    ror(std::integral_constant<int, 0x122>{});
+    ror(std::integral_constant<int, 0x121>{});
+    return v;
+}
+
+// Sum of lanes 0 .. n - 1 of v (the token's n exchange words), in every lane. The
+// butterfly again: adding the 16 words of an 8192-wide token in lane order
+// took 16 LDS-crossbar shuffles, or 16 dependent lane reads (below).
+__device__ __forceinline__ float lanes_sum(float v, int n, int lane) {
+    return wave_sum(lane < n ? v : 0.f);
+}
+
 // Residual-add + RMSNorm of one chunk after its all-reduce result o. The
 // token's sum of squares is combined across the waves of the workgroup (LDS)
 // and across the token's Q workgroups (epoch-tagged exchange words, double
@@ -497,9 +532,7 @@ __device__ __forceinline__ void residual_rmsnorm(const ReduceArgs &a, const Chun
 #pragma unroll
         for (int i = 0; i < kVec; ++i) ss = __builtin_fmaf(x[i], x[i], ss);
     }
-    // Butterfly: every lane ends with the bit-identical wave total.
-#pragma unroll
-    for (int off = kLanes / 2; off >= 1; off >>= 1) ss = ss + __shfl_xor(ss, off);
+    ss = wave_sum(ss);
 
     __shared__ float part[kMaxWavesPerGroup];
     __shared__ float total;
@@ -530,9 +563,7 @@ __device__ __forceinline__ void residual_rmsnorm(const ReduceArgs &a, const Chun
                 ready = __ballot(lane < Q && static_cast<uint32_t>(mine >> 32) != g) == 0;
             } while (!ready && ++spins < a.spin_limit);
             if (!ready && lane == 0) latch(a.err, kErrExchange, g, k.c, spins);
-            const float pv = __uint_as_float(static_cast<uint32_t>(mine));
-            float tot = 0.f;
-            for (int j = 0; j < Q; ++j) tot = tot + __shfl(pv, j);
+            const float tot = lanes_sum(__uint_as_float(static_cast<uint32_t>(mine)), Q, lane);
             if (lane == 0) total = tot;
         }
         __syncthreads();
@@ -632,55 +663,54 @@ __global__ __launch_bounds__(1024) void reduce_kernel(const uint32_t *ep_base, u
 // The persistent step's epilogue in two halves, so that the wait for the
 // token's other groups overlaps the next epoch's reduction instead of
 // stalling every chunk of the token once per epoch. Only the residual carries
-// from one epoch to the next, and it is this chunk's own; the token-wide sum of
-// squares is needed for y alone. epi_stage runs right after epoch g's sum: it
-// updates the residual, reduces this group's sum of squares and publishes it
-// in exchange plane g mod kExchPlanes. epi_finish runs one epoch later, or
-// after the step's last epoch: it waits for the token's Q words of epoch g,
-// adds them in group order and writes y. The arithmetic and its order are
+// from one epoch to the next, and it is this chunk's own (it stays in
+// registers for the whole step and is stored at its end); the token-wide sum
+// of squares is needed for y alone. epi_stage runs right after epoch g's sum:
+// it updates the residual, reduces this group's sum of squares and publishes
+// it in exchange plane g mod kExchPlanes. epi_finish runs one epoch later, or
+// after the step's last epoch: it takes the token's Q words of epoch g,
+// adds them (lanes_sum) and writes y. The arithmetic and its order are
 // residual_rmsnorm's. Four planes suffice: a group can publish epoch g + 4
 // only after finishing epoch g + 2, which needs every group's word of g + 2,
 // and a group publishes that only after it finished epoch g.
 struct EpiPending {
-    float x[kVec];  // res' of this lane's 8 elements, widened to fp32
-    float grp;      // this workgroup's sum of squares
-    uint32_t g;     // the epoch
+    V16 res;    // res' of this lane's 8 elements
+    float grp;  // this workgroup's sum of squares
+    uint32_t g; // the epoch
 };
 
+template <bool GROUPED>
 __device__ __forceinline__ void epi_stage(const ReduceArgs &a, const Chunk &k, uint32_t g,
-                                          const V16 &o, const V16 &rv, int lane, int wave, int G,
+                                          const V16 &o, V16 &res, int lane, int wave, int G,
                                           int q, bool xlocal, EpiPending &pd) {
-    V16 nr;
+    float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float a0 = lo_f32(o.w[i]), a1 = hi_f32(o.w[i]);
-        nr.w[i] = pack_bf16(a0 + lo_f32(rv.w[i]), a1 + hi_f32(rv.w[i]));
-        pd.x[2 * i] = lo_f32(nr.w[i]);
-        pd.x[2 * i + 1] = hi_f32(nr.w[i]);
+        res.w[i] = pack_bf16(a0 + lo_f32(res.w[i]), a1 + hi_f32(res.w[i]));
+        const float x0 = lo_f32(res.w[i]), x1 = hi_f32(res.w[i]);
+        ss = __builtin_fmaf(x0, x0, ss);
+        ss = __builtin_fmaf(x1, x1, ss);
     }
-    if (k.lane_ok) st16(a.residual + k.row, nr);
+    ss = wave_sum(k.lane_ok ? ss : 0.f);
+    pd.res = res;
 
-    float ss = 0.f;
-    if (k.lane_ok) {
-#pragma unroll
-        for (int i = 0; i < kVec; ++i) ss = __builtin_fmaf(pd.x[i], pd.x[i], ss);
+    pd.grp = ss;
+    if (GROUPED) {
+        __shared__ float part[kMaxWavesPerGroup];
+        if (lane == 0) part[wave] = ss;
+        __syncthreads();
+        float grp = 0.f;
+        for (int w = 0; w < G; ++w) grp = grp + part[w];
+        pd.grp = grp;
     }
-#pragma unroll
-    for (int off = kLanes / 2; off >= 1; off >>= 1) ss = ss + __shfl_xor(ss, off);
-
-    __shared__ float part[kMaxWavesPerGroup];
-    if (lane == 0) part[wave] = ss;
-    __syncthreads();
-    float grp = 0.f;
-    for (int w = 0; w < G; ++w) grp = grp + part[w];
-    pd.grp = grp;
     pd.g = g;
 
     const int Q = a.groups_per_token;
     if (Q > 1 && wave == 0 && lane == 0) {
         uint64_t *ex = a.exch + static_cast<size_t>(g % kExchPlanes) * a.exch_parity_stride +
                        static_cast<size_t>(k.t) * Q;
-        const uint64_t word = (static_cast<uint64_t>(g) << 32) | __float_as_uint(grp);
+        const uint64_t word = (static_cast<uint64_t>(g) << 32) | __float_as_uint(pd.grp);
         // all groups of the token on this XCD: the word meets them in its L2
         if (xlocal)
             __hip_atomic_store(ex + q, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -689,47 +719,56 @@ __device__ __forceinline__ void epi_stage(const ReduceArgs &a, const Chunk &k, u
     }
 }
 
-// `y` is the ring entry of epoch pd.g. (`pd` by value: with a reference the
+// This lane's exchange word of epoch g (lanes >= Q read group Q - 1's).
+__device__ __forceinline__ uint64_t epi_word(const ReduceArgs &a, const Chunk &k, uint32_t g,
+                                             int lane) {
+    const int Q = a.groups_per_token;
+    const uint64_t *ex = a.exch + static_cast<size_t>(g % kExchPlanes) * a.exch_parity_stride +
+                         static_cast<size_t>(k.t) * Q;
+    return __hip_atomic_load(ex + (lane < Q ? lane : Q - 1), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// `y` is the ring entry of epoch pd.g, `mine` this lane's exchange word of it
+// as loaded before the reduction of the epoch after (usually every group's is
+// there by then). (`pd` by value: with a reference the
 // compiler kept the pending state in scratch memory.) True in wave 0 when the
 // exchange wait failed: it ran out of polls (latched here), or found an error
 // latched elsewhere.
+template <bool GROUPED>
 __device__ __forceinline__ bool epi_finish(const ReduceArgs &a, const Chunk &k,
-                                           const EpiPending pd, const V16 &wv, uint16_t *y,
-                                           int lane, int wave) {
+                                           const EpiPending pd, uint64_t mine, const V16 &wv,
+                                           uint16_t *y, int lane, int wave) {
     const int Q = a.groups_per_token;
     float tot = pd.grp;
     bool failed = false;
     if (Q > 1) {
-        __shared__ float total;
         if (wave == 0) {
-            const uint64_t *ex = a.exch +
-                                 static_cast<size_t>(pd.g % kExchPlanes) * a.exch_parity_stride +
-                                 static_cast<size_t>(k.t) * Q;
-            uint64_t mine = 0;
             uint32_t spins = 0;
-            bool ready;
-            do {
-                if (lane < Q)
-                    mine = __hip_atomic_load(ex + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ready = __ballot(lane < Q && static_cast<uint32_t>(mine >> 32) != pd.g) == 0;
-                if (!ready && spins >= kErrPollAfter && ld_relaxed(a.err) != 0) break;
-            } while (!ready && ++spins < a.spin_limit);
+            bool ready = __ballot(static_cast<uint32_t>(mine >> 32) != pd.g) == 0;
+            while (!ready) {
+                if (spins >= kErrPollAfter && ld_relaxed(a.err) != 0) break;
+                if (++spins >= a.spin_limit) break;
+                mine = epi_word(a, k, pd.g, lane);
+                ready = __ballot(static_cast<uint32_t>(mine >> 32) != pd.g) == 0;
+            }
             failed = !ready;
             if (!ready && lane == 0) latch(a.err, kErrExchange, pd.g, k.c, spins);
-            const float pv = __uint_as_float(static_cast<uint32_t>(mine));
-            float sum = 0.f;
-            for (int j = 0; j < Q; ++j) sum = sum + __shfl(pv, j);
-            if (lane == 0) total = sum;
+            tot = lanes_sum(__uint_as_float(static_cast<uint32_t>(mine)), Q, lane);
         }
-        __syncthreads();
-        tot = total;
+        if (GROUPED) {
+            __shared__ float total;
+            if (wave == 0 && lane == 0) total = tot;
+            __syncthreads();
+            tot = total;
+        }
     }
     const float inv = 1.0f / __builtin_sqrtf(tot / static_cast<float>(a.geo.hidden) + a.eps);
     V16 yo;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const float w0 = lo_f32(wv.w[i]), w1 = hi_f32(wv.w[i]);
-        yo.w[i] = pack_bf16((pd.x[2 * i] * inv) * w0, (pd.x[2 * i + 1] * inv) * w1);
+        yo.w[i] = pack_bf16((lo_f32(pd.res.w[i]) * inv) * w0, (hi_f32(pd.res.w[i]) * inv) * w1);
     }
     if (k.lane_ok) st16(y + k.row, yo);
     return failed;
@@ -926,8 +965,11 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
                           tag_is_local(A.place + static_cast<size_t>(k.t) * geo.segs + lane * G, base);
         xlocal = __ballot(!mine) == 0;
     }
-    V16 wv;
-    if (EPI) wv = ld16(a.weight + k.elem);
+    V16 wv, res;
+    if (EPI) {
+        wv = ld16(a.weight + k.elem);
+        res = ld16(a.residual + k.row);
+    }
     EpiPending pending;   // the epilogue of the previous epoch, finished one epoch late
     bool have_pending = false;
     // Every lane polls a stamp of this chunk (lanes >= N repeat rank N - 1's,
@@ -948,8 +990,8 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
     for (int i = 0; i < A.reduces; ++i) {
         const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
         const uint32_t p = static_cast<uint32_t>(i + 1) & A.parity_mask;
-        V16 rv;
-        if (EPI) rv = ld16(a.residual + k.row);  // this wave's own previous store
+        uint64_t word = 0;  // the pending epoch's exchange word
+        if (EPI && have_pending && wave == 0) word = epi_word(a, k, pending.g, lane);
         V16 v[N];
         uint32_t attempts, first, last;
         const uint32_t st_first = st_next;
@@ -990,9 +1032,9 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
             st16_stream(a.out + ring + k.row, o);
         } else {
             EpiPending cur;
-            epi_stage(a, k, g, o, rv, lane, wave, G, bx, xlocal, cur);
-            if (have_pending &&
-                epi_finish(a, k, pending, wv, a.y + ring - A.ring_stride, lane, wave))
+            epi_stage<GROUPED>(a, k, g, o, res, lane, wave, G, bx, xlocal, cur);
+            if (have_pending && epi_finish<GROUPED>(a, k, pending, word, wv,
+                                                    a.y + ring - A.ring_stride, lane, wave))
                 stop = true;
             pending = cur;
             have_pending = true;
@@ -1004,15 +1046,18 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
         // unwritten: the step has failed). Every wait is bounded and reads the
         // error word once it has lasted kErrPollAfter polls, so a failure
         // anywhere ends the other waves' waits too.
-        if (GROUPED && EPI) {
-            if (__syncthreads_or(stop)) return;
-        } else if (stop) {
+        if (GROUPED && EPI) stop = __syncthreads_or(stop) != 0;
+        if (stop) {
+            if (EPI && k.lane_ok) st16(a.residual + k.row, res);
             return;
         }
     }
-    if (EPI && have_pending)
-        epi_finish(a, k, pending, wv, a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride,
-                   lane, wave);
+    if (EPI) {
+        if (k.lane_ok) st16(a.residual + k.row, res);
+        const uint64_t word = wave == 0 ? epi_word(a, k, pending.g, lane) : 0;
+        epi_finish<GROUPED>(a, k, pending, word, wv,
+                            a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane, wave);
+    }
 }
 
 // Grid (segs, plane_rows(tokens, segs), 2) of one-wave workgroups, or with the
@@ -1022,9 +1067,17 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
 // produces it. The last wave to arrive on the counter advances the epoch base
 // for the next step: every wave read the base before it arrived, so no wave
 // can see the advanced value.
+// (The occupancy asked for with the epilogue keeps the largest steps that init
+// accepts where they were.)
+constexpr int chain_occupancy(int n, bool epi, bool grouped) {
+    if (!epi) return 1;
+    if (!grouped) return 5;
+    return n <= 2 ? 6 : n <= 6 ? 5 : 4;
+}
+
 template <int N, int MODE, bool EPI, bool GROUPED, bool PREFETCH>
 __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
-                             1) void chain_kernel(ChainArgs A) {
+                             chain_occupancy(N, EPI, GROUPED)) void chain_kernel(ChainArgs A) {
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = GROUPED ? static_cast<int>(threadIdx.x) / kLanes : 0;
     const int G = GROUPED ? static_cast<int>(blockDim.x) / kLanes : 1;
