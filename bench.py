@@ -14,8 +14,8 @@ persistent kernel launch whose consumer waves poll the stamps before they load
 the payload (ORDERED: no speculation) while producer waves play the peers
 concurrently; --persistent 0 runs the per-epoch step, whose reduction is the
 paper's speculative one (SPEC): one launch with a workgroup barrier between
-all-reduces (with the epilogue, one buffer, unfused peers or more than 4096
-chunks: a captured graph with one launch per all-reduce).
+all-reduces (with one buffer, unfused peers or more chunks than fit the GPU: a
+captured graph with one launch per all-reduce).
 
 Printed JSON line (rank 0):
   value            microseconds per all-reduce over the timed steps (HIP events
@@ -70,9 +70,10 @@ def produce_bytes(N: int, T: int, H: int) -> int:
 
 def step_launches(L: int, chunks: int, persistent, fused, epilogue=False) -> int:
     """Kernel launches of one decode step: one for a persistent step and for a
-    plain per-epoch step with the peers one epoch ahead whose chunks fit the
-    GPU as two-wave workgroups (16 on each of 256 CUs)."""
-    if persistent or (fused and not epilogue and chunks <= 4096):
+    per-epoch step with the peers one epoch ahead whose chunks fit the GPU as
+    two-wave workgroups (16 on each of 256 CUs; with the epilogue a quarter of
+    10)."""
+    if persistent or (fused and chunks <= (640 if epilogue else 4096)):
         return 1
     return L + 2 if fused else 2 * L + 1
 

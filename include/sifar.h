@@ -230,12 +230,14 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
 /* Enqueue one decode step for `tokens` tokens: L all-reduces plus one
  * epoch-counter advance. A per-epoch step with fuse_peers runs in phases:
  * produce(g1), then L-1 phases that each reduce g_i while the peers write
- * g_(i+1), then reduce(g_L). A plain one whose chunks all fit the GPU at once
- * as two-wave workgroups (4096 chunks on MI355X) is one kernel launch: a
+ * g_(i+1), then reduce(g_L). One whose chunks all fit the GPU at once as
+ * two-wave workgroups (4096 chunks on MI355X; with the epilogue, a quarter of
+ * what fits, at least 640 chunks of at most 64 per token) is one kernel launch: a
  * workgroup is one chunk, its first wave the reduction, its second the peers,
  * and a workgroup barrier separates the phases. Any other is one
  * hipGraphLaunch of a kernel node per phase (L + 1); without fuse_peers, of
- * L x (produce, reduce). Outputs, logs and errors are the same either way.
+ * L x (produce, reduce). Outputs, logs and errors are the same either way (the
+ * epilogue's y within its tolerance).
  * A persistent step is one kernel launch for the whole
  * step (a one-node graph replay measured slower). In a persistent step the
  * peers run concurrently with the reduction, so a reduction often reaches an

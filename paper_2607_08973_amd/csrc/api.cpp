@@ -211,7 +211,7 @@ int chain_args(const sifar_t h, int32_t tokens, ChainArgs *ca) {
     } else {
         ca->r.out = static_cast<uint16_t *>(h->buf.out_ring);
     }
-    const int waves = chain_waves(h, tokens);
+    const int waves = h->cfg.persistent ? chain_waves(h, tokens) : 1;
     ca->r.groups_per_token = h->segs / waves;  // the epilogue's exchange width
     ca->reduces = L;
     ca->ring_stride = static_cast<uint64_t>(h->cfg.max_tokens) * h->cfg.hidden;
@@ -383,9 +383,18 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
         h->chain_grouping = c.nranks * kChainGroupWaves <= kLanes && gcap > 0 &&
                             waves / kChainGroupWaves <= gcap;
     }
-    if (!c.persistent && !c.epilogue && c.fuse_peers && c.buffers == 2 &&
-        step_offsets_fit(c.nranks, h->slot_elems))
-        h->step_cap = max_active_step_groups(c.nranks, c.validate);
+    if (!c.persistent && c.fuse_peers && c.buffers == 2 && (!c.epilogue || h->segs <= kLanes) &&
+        step_offsets_fit(c.nranks, h->slot_elems)) {
+        h->step_cap = max_active_step_groups(c.nranks, c.validate, c.epilogue != 0);
+        // With the epilogue a token's workgroups wait for each other. A
+        // quarter of the GPU's places leaves room for the steps of three more
+        // handles on other streams (a process has 4 hardware queues), which
+        // one launch per all-reduce could run beside each other.
+        if (c.epilogue) {
+            h->step_cap /= 4;
+            if (h->exch_q < h->segs) h->exch_q = h->segs;
+        }
+    }
     rc = SIFAR_OK;
     if (!rc) rc = dev_alloc(&h->slots, static_cast<size_t>(c.nranks) * 2 * h->slot_elems);
     if (!rc) rc = dev_alloc(&h->stamps, static_cast<size_t>(2) * h->w_max * c.nranks);
@@ -561,14 +570,15 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
     }
     // A per-epoch step in one launch wherever its workgroups fit at once (the
     // kernel's comment has both sides measured).
-    if (static_cast<int64_t>(tokens) * h->segs <= h->step_cap) {
+    if (static_cast<int64_t>(tokens) * h->segs <= h->step_cap &&
+        source_offsets_fit(h->cfg.nranks, h->buf.pool_rank_stride)) {
         if (base != h->base_host) {
             rc = hip_status(launch_set_base(&h->state->epoch_base, base, s));
             if (rc) return rc;
         }
         ChainArgs ca{};
         chain_args(h, tokens, &ca);
-        rc = hip_status(launch_step(ca, h->cfg.validate, s));
+        rc = hip_status(launch_step(ca, h->cfg.validate, h->cfg.epilogue != 0, s));
         if (rc) return rc;
         step_enqueued(h, tokens, base);
         return SIFAR_OK;

@@ -47,6 +47,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void *base) 
                                              kBufferWord3);
 }
 
+// ... of no bytes unless `on` (wave-uniform): loads through it return 0 and
+// stores are dropped by the bounds check, so a choice per rank needs no branch
+// (a branch would make the accesses on its far side wait for those before it).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc_if(const void *base, bool on) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(uniform_ptr(base)), 0,
+                                             on ? 0x7fffffff : 0, kBufferWord3);
+}
+
 typedef int V4i __attribute__((ext_vector_type(4)));
 
 // 16 bytes at byte offset `off` (per lane, below 2^31) from `base` (the same
@@ -72,18 +80,24 @@ __device__ __forceinline__ V16 ld16_agent(const void *base, uint32_t off) {
 }
 
 // 16 bytes at byte offset off + soff through the descriptor rs, made once
-// for several loads (per load only the scalar offset soff changes), with
-// ld16_agent's caching: past this CU's L1.
-__device__ __forceinline__ V16 ld16_agent_at(__amdgpu_buffer_rsrc_t rs, uint32_t off,
-                                             uint32_t soff) {
+// for several loads (per load only the scalar offset soff changes); POLICY as
+// for ld16_buffer.
+template <int POLICY = 0>
+__device__ __forceinline__ V16 ld16_at(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t soff) {
     const V4i x = __builtin_amdgcn_raw_buffer_load_b128(rs, static_cast<int>(off),
-                                                        static_cast<int>(soff), kCachePolicyAgent);
+                                                        static_cast<int>(soff), POLICY);
     V16 v;
     v.w[0] = static_cast<uint32_t>(x[0]);
     v.w[1] = static_cast<uint32_t>(x[1]);
     v.w[2] = static_cast<uint32_t>(x[2]);
     v.w[3] = static_cast<uint32_t>(x[3]);
     return v;
+}
+
+// ... with ld16_agent's caching: past this CU's L1.
+__device__ __forceinline__ V16 ld16_agent_at(__amdgpu_buffer_rsrc_t rs, uint32_t off,
+                                             uint32_t soff) {
+    return ld16_at<kCachePolicyAgent>(rs, off, soff);
 }
 
 // 16 bytes to byte offset off + soff through the descriptor rs (normal

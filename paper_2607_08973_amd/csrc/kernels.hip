@@ -1134,13 +1134,16 @@ __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
 // together), the rest of the sum that the loads' arrival does not cover, and
 // the issue of its stores; from 1024 chunks at N = 8 the bytes. Measured
 // against one launch per all-reduce (us per all-reduce, launches -> one
-// launch): N = 8, 4 tokens x 4096, 64 per step, 2.62 -> 0.62; with 10 % late
-// stamps 3.70 -> 1.28; 20 per step: N = 2, 1 x 4096, 2.59 -> 0.49; N = 8, 64 x
+// launch): N = 8, 4 tokens x 4096, 64 per step, 2.62 -> 0.58; with 10 % late
+// stamps 3.70 -> 1.20; 20 per step: N = 2, 1 x 4096, 2.59 -> 0.49; N = 8, 64 x
 // 4096, 3.69 -> 1.14; 64 x 8192, 5.49 -> 3.04; 256 x 8192 (4096 chunks, every
-// wave slot of the GPU), 16.3 -> 14.0; N = 2, 256 x 8192, 6.46 -> 3.92. It is
-// the faster one wherever its workgroups fit at once, so that is the rule;
-// beyond that, chunks would run their whole step one after another, which no
-// sequence of all-reduces does.
+// wave slot of the GPU), 16.3 -> 14.0; N = 2, 256 x 8192, 6.46 -> 3.92. With
+// the epilogue: 1 x 4096, 4.57 -> 1.13; 40 x 8192, 7.21 -> 1.71; 32 x 8192 with
+// 5 % late stamps, 120 per step, 10.6 -> 1.72. It is the faster one wherever its
+// workgroups fit at once, so that is the rule; beyond that, chunks would run
+// their whole step one after another, which no sequence of all-reduces does.
+// INJECT: the kernel that knows the injection table; without one the table's
+// branches leave the scalar registers (and 5 % of the time).
 
 // Phase boundary: orders the two waves' memory operations on their CU.
 __device__ __forceinline__ void phase_barrier() {
@@ -1151,46 +1154,70 @@ __device__ __forceinline__ void phase_barrier() {
 
 // The peers of one chunk. `done` (LDS): the last epoch of each parity that the
 // consumer of this launch has finished; the first epoch of each parity checks
-// the words that earlier launches left in memory.
-template <int N>
+// the words that earlier launches left in memory. Sources, slots and stage are
+// each addressed through one descriptor, every rank at a scalar offset (the
+// host checks that they fit 31 bits): pointers per rank overflow the scalar
+// registers.
+template <int N, bool INJECT>
 __device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base, const Chunk &k,
                                               int lane, uint32_t (&done)[2]) {
     const ProduceArgs &a = A.p;
     const Geometry &geo = a.geo;
+    const uint32_t off = lane_offset(geo, k);
+    const uint64_t first = chunk_first(geo, k);
+    const uint32_t rank_bytes = static_cast<uint32_t>(geo.slot_elems) * 4u;
+    const uint32_t src_bytes = static_cast<uint32_t>(a.rank_stride) * 2u;
     V16 v[N];
-    load_sources<N>(a, k, base + 1u, v);
+    auto load = [&](uint32_t g) {
+        const uint32_t e = mod_u32(g - 1u, a.entries_div);
+        const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(a.src + e * a.entry_stride + first);
+#pragma unroll
+        for (int r = 0; r < N; ++r) v[r] = ld16_at(rs, off, static_cast<uint32_t>(r) * src_bytes);
+    };
+    // Dual-buffer rule: a slot's previous epoch must have been consumed. The
+    // step's first two epochs follow earlier launches' words.
+    for (uint32_t i = 0; i < 2u && i < static_cast<uint32_t>(A.reduces); ++i) {
+        const size_t pc = static_cast<size_t>((i + 1u) & 1u) * geo.w_max + k.c;
+        const uint32_t prev = ld_relaxed(a.produced + pc), fin = ld_relaxed(a.consumed + pc);
+        if (lane == 0 && prev != fin) latch(a.err, kErrWaw, base + i + 1u, k.c, prev);
+    }
+    // the injection word travels with the sources
+    uint32_t word = 0;
+    if (INJECT) word = inject_word(a.inject, a.inject_div, base + 1u);
+    load(base + 1u);
     for (int i = 0; i < A.reduces; ++i) {
         const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
         const uint32_t p = static_cast<uint32_t>(i + 1) & 1u;
         const size_t pc = static_cast<size_t>(p) * geo.w_max + k.c;
-        // Dual-buffer rule: the slot's previous epoch must have been consumed.
-        uint32_t prev = g - 2u, fin;
-        if (i < 2) {
-            prev = ld_relaxed(a.produced + pc);
-            fin = ld_relaxed(a.consumed + pc);
-        } else {
-            fin = __hip_atomic_load(&done[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint64_t at = static_cast<uint64_t>(p) * geo.slot_elems + first;
+        if (i >= 2) {
+            const uint32_t fin =
+                __hip_atomic_load(&done[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (lane == 0 && fin != g - 2u) latch(a.err, kErrWaw, g, k.c, g - 2u);
         }
-        const uint32_t inj = inject_word(a.inject, a.inject_div, g);
-        if (a.stage && late_ranks(inj)) {
-            const uint32_t staged = late_ranks(inj);
-            const uint64_t at = static_cast<uint64_t>(p) * geo.slot_elems + k.row;
-            if (k.lane_ok) {
+        const uint32_t inj = INJECT ? __builtin_amdgcn_readfirstlane(word) : 0u;
+        const uint32_t staged = late_ranks(inj);
+        const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(a.slots + at);
+        // lanes past the row's end store the owning lane's bytes again: no
+        // branch, so nothing in flight is waited for beyond the data stored
+        if (!INJECT || staged == 0) {
 #pragma unroll
-                for (int r = 0; r < N; ++r)
-                    st16((((staged >> r) & 1u) ? a.stage : a.slots) + at + r * 2 * geo.slot_elems,
-                         v[r]);
-            }
+            for (int r = 0; r < N; ++r)
+                st16_at(rs, off, static_cast<uint32_t>(r) * rank_bytes, v[r]);
         } else {
-            store_slots_at<N>(a, k, p, v);
+#pragma unroll
+            for (int r = 0; r < N; ++r)
+                st16_at(buffer_rsrc((((staged >> r) & 1u) ? a.stage : a.slots) + at), off,
+                        static_cast<uint32_t>(r) * rank_bytes, v[r]);
         }
-        if (lane == 0 && prev != fin) latch(a.err, kErrWaw, g, k.c, prev);
         // the stamps follow the payload
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         if (lane < N && !((held_back(inj) >> lane) & 1u)) st_flag(a.stamps + pc * N + lane, g, true);
         if (lane == 0) st_flag(a.produced + pc, g, true);
-        // the next epoch's sources travel while the consumer works
-        if (i + 1 < A.reduces) load_sources<N>(a, k, g + 1u, v);
+        // the next epoch's sources travel while the consumer works (after the
+        // last epoch: harmless reads of the pool)
+        if (INJECT) word = inject_word(a.inject, a.inject_div, g + 1u);
+        load(g + 1u);
         phase_barrier();
     }
 }
@@ -1199,30 +1226,44 @@ __device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base,
 // their stamps: the ranks catch up.
 template <int N>
 __device__ __forceinline__ void catch_up(const ReduceArgs &a, const Chunk &k, uint32_t g,
-                                         uint32_t p, int lane, uint32_t *stamp) {
-    const uint32_t late = late_ranks(inject_word(a.inject, a.inject_div, g));
-    const uint64_t rank_step = 2 * a.geo.slot_elems;
-    const uint64_t at = static_cast<uint64_t>(p) * a.geo.slot_elems + k.row;
+                                         uint32_t p, uint32_t late, int lane, uint32_t *stamp) {
+    const uint32_t rank_bytes = static_cast<uint32_t>(a.geo.slot_elems) * 4u;
+    const uint64_t at = static_cast<uint64_t>(p) * a.geo.slot_elems + chunk_first(a.geo, k);
+    const uint32_t off = lane_offset(a.geo, k);
+    V16 x[N];
 #pragma unroll
-    for (int r = 0; r < N; ++r) {
-        if ((late >> r) & 1u) {
-            const V16 x = ld16(a.stage + at + r * rank_step);
-            if (k.lane_ok) st16(a.slots + at + r * rank_step, x);
-        }
-    }
+    for (int r = 0; r < N; ++r)
+        x[r] = ld16_at(buffer_rsrc_if(a.stage + at, (late >> r) & 1u), off,
+                       static_cast<uint32_t>(r) * rank_bytes);
+#pragma unroll
+    for (int r = 0; r < N; ++r)
+        st16_at(buffer_rsrc_if(a.slots + at, (late >> r) & 1u), off,
+                static_cast<uint32_t>(r) * rank_bytes, x[r]);
     // the payload is published before the stamps, as a peer would; both are
     // read again by this wave alone
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane < N && ((late >> lane) & 1u)) st_flag(stamp + lane, g, true);
 }
 
-template <int N, int MODE>
+template <int N, int MODE, bool EPI, bool INJECT>
 __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base, const Chunk &k,
                                               int lane, uint32_t (&done)[2]) {
     const ReduceArgs &a = A.r;
     const Geometry &geo = a.geo;
     const uint32_t off = lane_offset(geo, k);
     const uint32_t rank_bytes = static_cast<uint32_t>(geo.slot_elems) * 4u;
+    // the epilogue as in the persistent step: finished one epoch late
+    bool xlocal = false;
+    V16 wv, res;
+    EpiPending pending;
+    if (EPI) {
+        publish_place(A.place + k.c, base, lane);
+        xlocal = __ballot(lane < geo.segs &&
+                          !tag_is_local(A.place + static_cast<size_t>(k.t) * geo.segs + lane,
+                                        base)) == 0;
+        wv = ld16(a.weight + k.elem);
+        res = ld16(a.residual + k.row);
+    }
     for (int i = 0; i < A.reduces; ++i) {
         const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
         const uint32_t p = static_cast<uint32_t>(i + 1) & 1u;
@@ -1237,8 +1278,12 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
                 v[r] = ld16_agent_at(rs, off, static_cast<uint32_t>(r) * rank_bytes);
         };
         phase_barrier();
+        uint64_t word = 0;  // the previous epoch's exchange word
+        if (EPI && i > 0) word = epi_word(a, k, pending.g, lane);
         V16 v[N];
         uint32_t st = 0, attempts = 1, first = 0, last = 0;
+        uint32_t inj = 0;
+        if (INJECT) inj = inject_word(a.inject, a.inject_div, g);
         if (MODE != kOrdered) load(v);
         if (MODE != kNone) st = ld_relaxed(stamp_lane);
         // speculative: the sum runs as the payload arrives, the stamps decide
@@ -1255,7 +1300,9 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
                     if (lane == 0) latch(a.err, kErrRetryBudget, g, k.c, attempts);
                     break;
                 }
-                if (attempts == 1 && a.stage && m != 0) catch_up<N>(a, k, g, p, lane, stamp);
+                if (INJECT && attempts == 1 && m != 0)
+                    catch_up<N>(a, k, g, p, late_ranks(__builtin_amdgcn_readfirstlane(inj)), lane,
+                                stamp);
                 __atomic_signal_fence(__ATOMIC_SEQ_CST);
                 if (MODE != kOrdered) load(v);
                 st = ld_relaxed(stamp_lane);
@@ -1277,26 +1324,52 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
         write_log(a, k, g, log_word(attempts, first, last));
         write_stamp_log<N>(a, k, g, lane < N ? lane : N - 1, st_first, st);
         st_flag(a.consumed + pc, g, true);
-        // lanes past the row's end store the owning lane's bytes again
-        st16_stream(a.out + static_cast<uint64_t>(i) * A.ring_stride + k.row, o);
+        const uint64_t ring = static_cast<uint64_t>(i) * A.ring_stride;
+        if (!EPI) {
+            // lanes past the row's end store the owning lane's bytes again
+            st16_stream(a.out + ring + k.row, o);
+        } else {
+            EpiPending cur;
+            epi_stage<false>(a, k, g, o, res, lane, 0, 1, k.s, xlocal, cur);
+            if (i > 0)
+                epi_finish<false>(a, k, pending, word, wv, a.y + ring - A.ring_stride, lane, 0);
+            pending = cur;
+        }
+    }
+    if (EPI) {
+        if (k.lane_ok) st16(a.residual + k.row, res);
+        epi_finish<false>(a, k, pending, epi_word(a, k, pending.g, lane), wv,
+                          a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane, 0);
     }
 }
 
-// Grid (segs, tokens), two waves. The last workgroup to arrive on the counter
+// Grid (segs, tokens), two waves; with the epilogue (8 * ceil(tokens / 8) *
+// segs) with every workgroup of a token on one XCD, as in chain_kernel
+// (workgroups past the last token only arrive on the counter). The last workgroup to arrive on the counter
 // advances the epoch base for the next step: both waves of every workgroup
 // read it before their first barrier.
-template <int N, int MODE>
-__global__ __launch_bounds__(2 * kLanes, 8) void step_kernel(ChainArgs A) {
+template <int N, int MODE, bool EPI, bool INJECT>
+__global__ __launch_bounds__(2 * kLanes, EPI ? 5 : 8) void step_kernel(ChainArgs A) {
     __shared__ uint32_t done[2];
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kLanes);
     const uint32_t base = A.r.ep.base[0];
-    const Chunk k = chunk_at(A.r.geo, blockIdx.y, blockIdx.x, lane);
-    if (wave == 1) {
-        step_producer<N>(A, base, k, lane, done);
+    int bx = blockIdx.x, by = blockIdx.y;
+    if (EPI) {
+        const int j = static_cast<int>(blockIdx.x) >> 3;
+        bx = j % A.r.geo.segs;
+        by = (static_cast<int>(blockIdx.x) & 7) + 8 * (j / A.r.geo.segs);
+    }
+    if (!EPI || by < A.r.geo.tokens) {
+        const Chunk k = chunk_at(A.r.geo, by, bx, lane);
+        if (wave == 1) {
+            step_producer<N, INJECT>(A, base, k, lane, done);
+            return;
+        }
+        step_consumer<N, MODE, EPI, INJECT>(A, base, k, lane, done);
+    } else if (wave == 1) {
         return;
     }
-    step_consumer<N, MODE>(A, base, k, lane, done);
     if (lane == 0) {
         const uint32_t before =
             __hip_atomic_fetch_add(A.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1405,26 +1478,39 @@ const void *chain_fn_any(int nranks, int mode, bool epi, bool grouped, bool pref
     return nullptr;
 }
 
+// `inject`: the kernel that knows the injection table and the stage. NONE
+// validates nothing, so it has no injection.
+template <int N, int MODE>
+const void *step_fn(bool epi, bool inject) {
+    if (!inject)
+        return epi ? reinterpret_cast<const void *>(step_kernel<N, MODE, true, false>)
+                   : reinterpret_cast<const void *>(step_kernel<N, MODE, false, false>);
+    if (MODE == kNone) return nullptr;
+    constexpr int M = MODE == kNone ? kSpec : MODE;
+    return epi ? reinterpret_cast<const void *>(step_kernel<N, M, true, true>)
+               : reinterpret_cast<const void *>(step_kernel<N, M, false, true>);
+}
+
 template <int N>
-const void *step_fn_n(int mode) {
+const void *step_fn_n(int mode, bool epi, bool inject) {
     switch (mode) {
-        case kSpec: return reinterpret_cast<const void *>(step_kernel<N, kSpec>);
-        case kOrdered: return reinterpret_cast<const void *>(step_kernel<N, kOrdered>);
-        case kNone: return reinterpret_cast<const void *>(step_kernel<N, kNone>);
+        case kSpec: return step_fn<N, kSpec>(epi, inject);
+        case kOrdered: return step_fn<N, kOrdered>(epi, inject);
+        case kNone: return step_fn<N, kNone>(epi, inject);
     }
     return nullptr;
 }
 
-const void *step_fn_any(int nranks, int mode) {
+const void *step_fn_any(int nranks, int mode, bool epi, bool inject) {
     switch (nranks) {
-        case 1: return step_fn_n<1>(mode);
-        case 2: return step_fn_n<2>(mode);
-        case 3: return step_fn_n<3>(mode);
-        case 4: return step_fn_n<4>(mode);
-        case 5: return step_fn_n<5>(mode);
-        case 6: return step_fn_n<6>(mode);
-        case 7: return step_fn_n<7>(mode);
-        case 8: return step_fn_n<8>(mode);
+        case 1: return step_fn_n<1>(mode, epi, inject);
+        case 2: return step_fn_n<2>(mode, epi, inject);
+        case 3: return step_fn_n<3>(mode, epi, inject);
+        case 4: return step_fn_n<4>(mode, epi, inject);
+        case 5: return step_fn_n<5>(mode, epi, inject);
+        case 6: return step_fn_n<6>(mode, epi, inject);
+        case 7: return step_fn_n<7>(mode, epi, inject);
+        case 8: return step_fn_n<8>(mode, epi, inject);
     }
     return nullptr;
 }
@@ -1532,18 +1618,27 @@ hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, 
     return hipLaunchKernel(fn, grid, dim3(kLanes * waves), args, 0, s);
 }
 
-hipError_t launch_step(const ChainArgs &a, int mode, hipStream_t s) {
-    const void *fn = step_fn_any(a.r.geo.nranks, mode);
-    if (!fn || a.parity_mask != 1u || !a.r.stamp_log) return hipErrorInvalidValue;
-    // the slots are addressed at 32-bit offsets from rank 0's
-    if (!step_offsets_fit(a.r.geo.nranks, a.r.geo.slot_elems)) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<uint32_t>(a.r.geo.segs), static_cast<uint32_t>(a.r.geo.tokens));
+hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, hipStream_t s) {
+    const void *fn = step_fn_any(a.r.geo.nranks, mode, epilogue, a.p.stage != nullptr);
+    if (epilogue && (a.r.geo.segs > kLanes || a.r.groups_per_token != a.r.geo.segs))
+        return hipErrorInvalidValue;
+    if (!fn || a.parity_mask != 1u || !a.r.stamp_log || (a.p.inject && !a.p.stage)) return hipErrorInvalidValue;
+    // slots and sources are addressed at 32-bit offsets from rank 0's
+    if (!step_offsets_fit(a.r.geo.nranks, a.r.geo.slot_elems) ||
+        !source_offsets_fit(a.r.geo.nranks, a.p.rank_stride))
+        return hipErrorInvalidValue;
+    const uint32_t segs = static_cast<uint32_t>(a.r.geo.segs);
+    const uint32_t tokens = static_cast<uint32_t>(a.r.geo.tokens);
+    const dim3 grid = epilogue ? dim3((tokens + 7u) / 8u * 8u * segs) : dim3(segs, tokens);
     void *args[] = {const_cast<ChainArgs *>(&a)};
     return hipLaunchKernel(fn, grid, dim3(2 * kLanes), args, 0, s);
 }
 
-int max_active_step_groups(int nranks, int mode) {
-    return resident_groups(step_fn_any(nranks, mode), 2 * kLanes);
+int max_active_step_groups(int nranks, int mode, bool epilogue) {
+    const int lean = resident_groups(step_fn_any(nranks, mode, epilogue, false), 2 * kLanes);
+    const void *fn = step_fn_any(nranks, mode, epilogue, true);
+    const int full = fn ? resident_groups(fn, 2 * kLanes) : lean;
+    return full < lean ? full : lean;
 }
 
 int max_active_groups(int nranks, int mode, bool epilogue, int waves_per_group) {

@@ -176,10 +176,13 @@ hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, 
 inline bool step_offsets_fit(int nranks, uint64_t slot_elems) {
     return static_cast<uint64_t>(nranks) * 4u * slot_elems <= 0x7fffffffull;
 }
-// Per-epoch step in one launch (plain, dual buffers): grid (segs, tokens) of
-// two-wave workgroups, and how many of them can be resident at once.
-hipError_t launch_step(const ChainArgs &a, int mode, hipStream_t s);
-int max_active_step_groups(int nranks, int mode);
+inline bool source_offsets_fit(int nranks, int64_t rank_stride) {
+    return rank_stride <= 0x7fffffffll / 2 / nranks;
+}
+// Per-epoch step in one launch (dual buffers): a two-wave workgroup per chunk,
+// and how many of them can be resident at once.
+hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, hipStream_t s);
+int max_active_step_groups(int nranks, int mode, bool epilogue);
 hipError_t launch_advance(uint32_t *epoch_base, uint32_t step, hipStream_t s);
 hipError_t launch_set_base(uint32_t *epoch_base, uint32_t value, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, uint64_t count, hipStream_t s);

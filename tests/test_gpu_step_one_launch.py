@@ -1,4 +1,4 @@
-"""Per-epoch steps in one launch (plain, dual buffers, peers one epoch ahead)
+"""Per-epoch steps in one launch (dual buffers, peers one epoch ahead)
 against the same steps as separate producer and reduction launches
 (fuse_peers = 0) and the oracle: outputs, decision log and raw stamps must be
 the same words, whatever the shape, validation mode, chain length, injected
@@ -11,7 +11,7 @@ import torch
 
 import oracle
 import synth
-from sifar_harness import StepRun, inject_table, to_host
+from sifar_harness import StepRun, inject_table, to_host, ulp_distance
 
 pytestmark = pytest.mark.gpu
 
@@ -120,3 +120,80 @@ def test_withheld_stamp_in_one_launch_latches():
     log = r.s.read_log()[2, :4]
     assert np.all((log & 0xFFFF) == 7) and np.all((log >> 24) == 4)
     r.s.close()
+
+
+@pytest.mark.parametrize("N,T,H,L,G,p", [(8, 3, 8192, 6, 1, 0.3), (5, 9, 1000, 5, 2, 0.1),
+                                         (1, 1, 520, 1, 1, 0.0), (2, 40, 8192, 3, 4, 0.1)])
+@pytest.mark.parametrize("mode", ["spec", "ordered"])
+def test_epilogue_one_launch_equals_separate_launches(N, T, H, L, G, p, mode):
+    w = synth.Workload(87, f"one-launch-epi-{N}-{T}-{H}", N, (T,), H, L, 1, "act", epilogue=True)
+    a = StepRun(w, T, validate=mode, fuse_peers=1)
+    b = StepRun(w, T, validate=mode, fuse_peers=0, waves_per_group=G, pool=a.pool)
+    if p:
+        late = synth.delay_table(87, N, 2 * L + 1, p)
+        for r in (a, b):
+            r.s.set_injection(inject_table(late))
+    res = a.res0.copy()
+    for step in range(3):
+        print(f"epilogue one launch N={N} T={T} H={H} {mode} step {step}", flush=True)
+        ea, eb = a.step(T), b.step(T)
+        assert ea == eb
+        _, r_list, y_list = oracle.reduce_chain(a.pool, ea, T, epilogue=(res, a.weight, w.rms_eps))
+        y = to_host(a.y_d)
+        for i in range(L):
+            assert ulp_distance(y[i], y_list[i]).max() <= 1, f"step={step} node={i}"
+        for r in (a, b):
+            assert np.array_equal(to_host(r.res_d), r_list[-1]), f"residual, step={step}"
+        _same_words(a, b, T, ea)
+        res = r_list[-1]
+    for r in (a, b):
+        r.s.check()
+        r.s.close()
+
+
+def test_epilogue_batches_on_both_sides_of_the_launch_rule():
+    """With the epilogue a step is one launch up to a quarter of the GPU's places
+    (640 to 1024 chunks by rank count), a graph of launches beyond: one handle
+    crosses the line both ways, and an eager epoch follows."""
+    N, H, L, T_max = 2, 8192, 4, 66
+    w = synth.Workload(88, "one-launch-epi-or-graph", N, (T_max,), H, L, 1, "act", epilogue=True)
+    pool = synth.payload_pool(88, N, T_max, H, 5, "act")
+    r = StepRun(w, T_max, pool=pool)
+    res = r.res0.copy()
+    for tokens in (40, 66, 1, 64, 65, 33):
+        print(f"epilogue launch rule T={tokens}", flush=True)
+        epochs = r.step(tokens)
+        _, r_list, y_list = oracle.reduce_chain(pool, epochs, tokens,
+                                                epilogue=(res[:tokens], r.weight, w.rms_eps))
+        res[:tokens] = r_list[-1]
+        assert np.array_equal(to_host(r.res_d), res), tokens
+        y = to_host(r.y_d)
+        for i in range(L):
+            assert ulp_distance(y[i, :tokens], y_list[i]).max() <= 1, (tokens, i)
+    r.s.check()
+    r.s.close()
+
+
+def test_epilogue_steps_of_four_handles_at_once():
+    """Four handles' one-launch epilogue steps on four streams: their token
+    exchanges wait inside the launches, so all must fit the GPU together."""
+    N, T, H, L = 8, 32, 8192, 8
+    w = synth.Workload(89, "one-launch-epi-4", N, (T,), H, L, 1, "act", epilogue=True)
+    pool = synth.payload_pool(89, N, T, H, 5, "act")
+    runs = [StepRun(w, T, pool=pool) for _ in range(4)]
+    streams = [torch.cuda.Stream() for _ in runs]
+    torch.cuda.synchronize()
+    for step in range(6):
+        print(f"four handles step {step}", flush=True)
+        for r, st in zip(runs, streams):
+            r.s.step(T, st)
+    torch.cuda.synchronize()
+    res = runs[0].res0.copy()
+    for step in range(6):
+        epochs = range(1 + step * L, 1 + (step + 1) * L)
+        _, r_list, _ = oracle.reduce_chain(pool, epochs, T, epilogue=(res, runs[0].weight, w.rms_eps))
+        res = r_list[-1]
+    for r in runs:
+        r.s.check()
+        assert np.array_equal(to_host(r.res_d), res)
+        r.s.close()
