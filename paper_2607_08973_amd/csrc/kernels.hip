@@ -1175,16 +1175,20 @@ __device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base,
         for (int r = 0; r < N; ++r) v[r] = ld16_at(rs, off, static_cast<uint32_t>(r) * src_bytes);
     };
     // Dual-buffer rule: a slot's previous epoch must have been consumed. The
-    // step's first two epochs follow earlier launches' words.
-    for (uint32_t i = 0; i < 2u && i < static_cast<uint32_t>(A.reduces); ++i) {
-        const size_t pc = static_cast<size_t>((i + 1u) & 1u) * geo.w_max + k.c;
-        const uint32_t prev = ld_relaxed(a.produced + pc), fin = ld_relaxed(a.consumed + pc);
-        if (lane == 0 && prev != fin) latch(a.err, kErrWaw, base + i + 1u, k.c, prev);
-    }
-    // the injection word travels with the sources
+    // step's first two epochs follow earlier launches' words, which travel with
+    // the first sources (a round trip of their own ahead of them cost 0.5 us a
+    // step), as does the injection word.
+    const uint32_t prev1 = ld_relaxed(a.produced + geo.w_max + k.c);
+    const uint32_t fin1 = ld_relaxed(a.consumed + geo.w_max + k.c);
+    const uint32_t prev2 = ld_relaxed(a.produced + k.c);
+    const uint32_t fin2 = ld_relaxed(a.consumed + k.c);
     uint32_t word = 0;
     if (INJECT) word = inject_word(a.inject, a.inject_div, base + 1u);
     load(base + 1u);
+    if (lane == 0) {
+        if (prev1 != fin1) latch(a.err, kErrWaw, base + 1u, k.c, prev1);
+        if (A.reduces > 1 && prev2 != fin2) latch(a.err, kErrWaw, base + 2u, k.c, prev2);
+    }
     for (int i = 0; i < A.reduces; ++i) {
         const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
         const uint32_t p = static_cast<uint32_t>(i + 1) & 1u;
