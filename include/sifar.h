@@ -417,7 +417,8 @@ int sifar_litmus(int32_t protocol, int32_t placement, int32_t pairs, int32_t tri
  * (src + r * src_rank_stride elements, laid out [tokens][hidden]) into a slot
  * and stamp it with the call's epoch, then the speculative reduction
  * validates the stamps and writes the fixed-order fp32 sum, rounded to bf16,
- * to out[tokens][hidden]. Two kernel launches on `stream`; nothing is
+ * to out[tokens][hidden]. One kernel launch on `stream`, a workgroup barrier
+ * between each chunk's peers and its reduction; nothing is
  * allocated or freed (no hipMalloc, hipFree or other allocating call), and
  * nothing synchronises.
  *
@@ -429,8 +430,8 @@ int sifar_litmus(int32_t protocol, int32_t placement, int32_t pairs, int32_t tri
  * (host-side count per device), so a stamp of an earlier call is always
  * stale. Calls that overlap on one GPU (other streams, other host threads
  * without ordering) race on the array and may return wrong sums; calls
- * ordered on one stream never do, and then the producer's launch completes
- * before the reduction's, so no validation fails and no device error arises.
+ * ordered on one stream never do, and then a chunk's peers are done before
+ * its reduction starts, so no validation fails and no device error arises.
  *
  * Limits: 1 <= nranks <= 8; hidden a multiple of 8 in 8..65536;
  * 1 <= tokens <= SIFAR_NOALLOC_MAX_TOKENS; tokens * hidden <=

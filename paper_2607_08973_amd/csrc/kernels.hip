@@ -1384,6 +1384,77 @@ __global__ __launch_bounds__(2 * kLanes, EPI ? 5 : 8) void step_kernel(ChainArgs
     }
 }
 
+// ---------------------------------------------------------------------------
+// One all-reduce in one launch (the allocation-free call): the phases of
+// step_kernel for a single epoch. Wave 1 of a chunk's workgroup plays the
+// peers, a barrier follows, wave 0 loads payload and stamps together, sums as
+// they arrive and validates. What bounds it: one launch, a round trip for the
+// sources and one for the payload. As a producer and a reduction launch the
+// call took 10.9 us (N = 8, 16 tokens x 4096, calls back to back from Python),
+// 7.3 so, most of it the caller's.
+// The arguments up to the source loads lead, to be preloaded into scalar
+// registers; the epoch itself is one of them.
+template <int N>
+__global__ __launch_bounds__(2 * kLanes, 8) void once_kernel(const uint16_t *src,
+                                                             int64_t rank_stride, uint16_t *slots,
+                                                             uint64_t slot_elems, uint32_t *stamps,
+                                                             uint32_t g, int32_t hidden,
+                                                             int32_t segs, int32_t w_max,
+                                                             OnceArgs a) {
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kLanes);
+    Geometry geo{};
+    geo.hidden = hidden;
+    geo.segs = segs;
+    const Chunk k = chunk_at(geo, blockIdx.y, blockIdx.x, lane);
+    const uint32_t p = g & 1u;
+    const size_t pc = static_cast<size_t>(p) * w_max + k.c;
+    const uint64_t at = static_cast<uint64_t>(p) * slot_elems + chunk_first(geo, k);
+    const uint32_t off = lane_offset(geo, k);
+    const uint32_t rank_bytes = static_cast<uint32_t>(slot_elems) * 4u;
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(slots + at);
+    uint32_t *stamp = stamps + pc * N;
+    V16 v[N];
+    if (wave == 1) {
+#pragma unroll
+        for (int r = 0; r < N; ++r) v[r] = ld16(src + r * rank_stride + k.row);
+        const uint32_t prev = ld_relaxed(a.produced + pc), fin = ld_relaxed(a.consumed + pc);
+#pragma unroll
+        for (int r = 0; r < N; ++r) st16_at(rs, off, static_cast<uint32_t>(r) * rank_bytes, v[r]);
+        if (lane == 0 && prev != fin) latch(a.err, kErrWaw, g, k.c, prev);
+        // the stamps follow the payload
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        if (lane < N) st_flag(stamp + lane, g, true);
+        if (lane == 0) st_flag(a.produced + pc, g, true);
+        phase_barrier();
+        return;
+    }
+    phase_barrier();
+    uint32_t attempts = 0, m = 0, first = 0;
+    V16 o;
+    while (true) {
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+            v[r] = ld16_agent_at(rs, off, static_cast<uint32_t>(r) * rank_bytes);
+        const uint32_t st = ld_relaxed(stamp + (lane < N ? lane : N - 1));
+        o = sum_round<N>(v);
+        m = static_cast<uint32_t>(__ballot(lane < N && st != g));
+        if (attempts++ == 0) first = m;
+        // a stale stamp can only come from a call that overlaps this one
+        if (m == 0) break;
+        if (attempts >= a.max_attempts) {
+            if (lane == 0) latch(a.err, kErrRetryBudget, g, k.c, attempts);
+            break;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    if (lane == 0) {
+        a.log[k.c] = log_word(attempts, first, m);
+        a.consumed[pc] = g;
+    }
+    if (k.lane_ok) st16_stream(a.out + k.row, o);
+}
+
 __global__ void advance_kernel(uint32_t *base, uint32_t step) {
     if (threadIdx.x == 0) base[0] += step;
 }
@@ -1620,6 +1691,30 @@ hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, 
                                : dim3(q, static_cast<uint32_t>(plane_rows(a.r.geo.tokens, q)), 2);
     void *args[] = {const_cast<ChainArgs *>(&a)};
     return hipLaunchKernel(fn, grid, dim3(kLanes * waves), args, 0, s);
+}
+
+hipError_t launch_once(const Geometry &geo, uint32_t g, const uint16_t *src, int64_t rank_stride,
+                       uint16_t *slots, uint32_t *stamps, const OnceArgs &a, hipStream_t s) {
+    if (!step_offsets_fit(geo.nranks, geo.slot_elems)) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<uint32_t>(geo.segs), static_cast<uint32_t>(geo.tokens));
+#define SIFAR_ONCE(N_)                                                                             \
+    case N_:                                                                                       \
+        hipLaunchKernelGGL(once_kernel<N_>, grid, dim3(2 * kLanes), 0, s, src, rank_stride, slots, \
+                           geo.slot_elems, stamps, g, geo.hidden, geo.segs, geo.w_max, a);         \
+        break
+    switch (geo.nranks) {
+        SIFAR_ONCE(1);
+        SIFAR_ONCE(2);
+        SIFAR_ONCE(3);
+        SIFAR_ONCE(4);
+        SIFAR_ONCE(5);
+        SIFAR_ONCE(6);
+        SIFAR_ONCE(7);
+        SIFAR_ONCE(8);
+        default: return hipErrorInvalidValue;
+    }
+#undef SIFAR_ONCE
+    return hipGetLastError();
 }
 
 hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, hipStream_t s) {

@@ -2,8 +2,9 @@
 // (the peers' write, then the speculative reduction, Sec. 3.5 and 4.2) with
 // every piece of library state -- slots, stamps, consumed/produced words, the
 // decision log, the epoch base and the error word -- in one static device
-// array, for callers that cannot allocate device memory. It runs the same
-// producer and reduction kernels as sifar_produce + sifar_reduce.
+// array, for callers that cannot allocate device memory. One launch runs the
+// peers and the reduction of each chunk in a workgroup of its own, with a
+// barrier between them.
 //
 // The array's name is a host-side stand-in in host code, not a device
 // address: each GPU holds its own copy at its own address, which
@@ -90,42 +91,17 @@ extern "C" int sifar_allreduce_noalloc(const void *src, int64_t src_rank_stride,
     geo.segs = (hidden + kChunk - 1) / kChunk;
     geo.w_max = kWMax;
     geo.slot_elems = kSlotElems;
-    // the epoch is passed whole: base = the always-zero word
-    const EpochRef ep{&state->zero, g, g & 1u};
-
-    ProduceArgs pa{};
-    pa.geo = geo;
-    pa.ep = ep;
-    pa.slots = reinterpret_cast<uint16_t *>(base + kOffSlots);
-    pa.stamps = reinterpret_cast<uint32_t *>(base + kOffStamps);
-    pa.consumed = reinterpret_cast<const uint32_t *>(base + kOffConsumed);
-    pa.produced = reinterpret_cast<uint32_t *>(base + kOffProduced);
-    pa.src = static_cast<const uint16_t *>(src);
-    pa.entry_stride = 0;
-    pa.rank_stride = src_rank_stride;
-    pa.entries = 1;
-    pa.entries_div = make_div(1);
-    pa.inject_div = make_div(1);
-    pa.err = state->err;
-
-    ReduceArgs ra{};
-    ra.geo = geo;
-    ra.ep = ep;
-    ra.slots = pa.slots;
-    ra.stamps = pa.stamps;
-    ra.consumed = reinterpret_cast<uint32_t *>(base + kOffConsumed);
-    ra.log = reinterpret_cast<uint32_t *>(base + kOffLog);
-    ra.log_epochs = 1;
-    ra.log_div = make_div(1);
-    ra.inject_div = make_div(1);
-    ra.max_attempts = kAttempts;
-    ra.spin_limit = 1;
-    ra.out = static_cast<uint16_t *>(out);
-    ra.groups_per_token = 1;
-    ra.err = state->err;
-
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    if (launch_produce(pa, 1, s) != hipSuccess) return SIFAR_EHIP;
-    if (launch_reduce(ra, nullptr, kSpec, false, 1, s) != hipSuccess) return SIFAR_EHIP;
+    OnceArgs a{};
+    a.consumed = reinterpret_cast<uint32_t *>(base + kOffConsumed);
+    a.produced = reinterpret_cast<uint32_t *>(base + kOffProduced);
+    a.log = reinterpret_cast<uint32_t *>(base + kOffLog);
+    a.out = static_cast<uint16_t *>(out);
+    a.max_attempts = kAttempts;
+    a.err = state->err;
+    if (launch_once(geo, g, static_cast<const uint16_t *>(src), src_rank_stride,
+                    reinterpret_cast<uint16_t *>(base + kOffSlots),
+                    reinterpret_cast<uint32_t *>(base + kOffStamps), a,
+                    static_cast<hipStream_t>(stream)) != hipSuccess)
+        return SIFAR_EHIP;
     return SIFAR_OK;
 }

@@ -153,6 +153,17 @@ struct ChainArgs {
                                  // chunk: (base + 1) << 32 | 0x100 | XCD, written at step start
 };
 
+// One all-reduce of one epoch in one launch: what it needs beyond geometry,
+// sources, slots and stamps.
+struct OnceArgs {
+    uint32_t *consumed;          // [2][w_max]
+    uint32_t *produced;          // [2][w_max]
+    uint32_t *log;               // [w_max]
+    uint16_t *out;               // [tokens][hidden]
+    uint32_t max_attempts;
+    uint32_t *err;
+};
+
 enum Mode : int { kSpec = 0, kOrdered = 1, kNone = 2 };
 
 hipError_t launch_produce(const ProduceArgs &a, int waves_per_group, hipStream_t s);
@@ -179,6 +190,9 @@ inline bool step_offsets_fit(int nranks, uint64_t slot_elems) {
 inline bool source_offsets_fit(int nranks, int64_t rank_stride) {
     return rank_stride <= 0x7fffffffll / 2 / nranks;
 }
+// All-reduce of epoch g in one launch, a two-wave workgroup per chunk.
+hipError_t launch_once(const Geometry &geo, uint32_t g, const uint16_t *src, int64_t rank_stride,
+                       uint16_t *slots, uint32_t *stamps, const OnceArgs &a, hipStream_t s);
 // Per-epoch step in one launch (dual buffers): a two-wave workgroup per chunk,
 // and how many of them can be resident at once.
 hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, hipStream_t s);
