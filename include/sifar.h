@@ -233,8 +233,9 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
  * g_(i+1), then reduce(g_L). One whose chunks all fit the GPU at once as
  * two-wave workgroups (4096 chunks on MI355X; with the epilogue, a quarter of
  * what fits, at least 640 chunks of at most 64 per token) is one kernel launch: a
- * workgroup is one chunk, its first wave the reduction, its second the peers,
- * and a workgroup barrier separates the phases. Any other is one
+ * workgroup is one chunk, its last wave the peers, the one (or, up to 256
+ * chunks, four) before it the reduction, and a workgroup barrier separates the
+ * phases. Any other is one
  * hipGraphLaunch of a kernel node per phase (L + 1); without fuse_peers, of
  * L x (produce, reduce). Outputs, logs and errors are the same either way (the
  * epilogue's y within its tolerance).

@@ -20,7 +20,8 @@ struct sifar_ctx {
     int groups_per_token = 1;
     bool chain_grouping = false;  // persistent steps may use kChainGroupWaves-wave workgroups
     bool chain_prefetch = false;  // one-wave persistent steps' producers load sources ahead
-    int step_cap = 0;             // workgroups of a one-launch per-epoch step that fit at once
+    int step_cap = 0;             // most chunks of a one-launch per-epoch step
+    int split_cap = 0;            // ... of one with kStepConsumers consumer waves per chunk
     uint64_t slot_elems = 0;
 
     uint16_t *slots = nullptr;     // [N][2][slot_elems]
@@ -187,6 +188,13 @@ int chain_waves(const sifar_ctx *h, int32_t tokens) {
                    chunks >= 512
                ? kChainGroupWaves
                : 1;
+}
+
+// Consumer waves per chunk of a one-launch per-epoch step (the kernel's comment
+// has both sides measured). With the epilogue each exchanges a word of its own.
+int step_consumers(const sifar_ctx *h, int32_t tokens) {
+    if (h->inject || (h->cfg.epilogue && h->segs * kStepConsumers > kLanes)) return 1;
+    return static_cast<int64_t>(tokens) * h->segs <= h->split_cap ? kStepConsumers : 1;
 }
 
 // Arguments of the persistent step kernel for `tokens` tokens; returns the
@@ -390,10 +398,13 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
         // quarter of the GPU's places leaves room for the steps of three more
         // handles on other streams (a process has 4 hardware queues), which
         // one launch per all-reduce could run beside each other.
+        h->split_cap = max_active_split_step_groups(c.nranks, c.validate, c.epilogue != 0);
         if (c.epilogue) {
             h->step_cap /= 4;
-            if (h->exch_q < h->segs) h->exch_q = h->segs;
+            h->split_cap /= 4;
+            h->exch_q = kLanes;  // a word for each of a token's consumer waves
         }
+        if (h->split_cap > kSplitChunks) h->split_cap = kSplitChunks;
     }
     rc = SIFAR_OK;
     if (!rc) rc = dev_alloc(&h->slots, static_cast<size_t>(c.nranks) * 2 * h->slot_elems);
@@ -578,7 +589,9 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
         }
         ChainArgs ca{};
         chain_args(h, tokens, &ca);
-        rc = hip_status(launch_step(ca, h->cfg.validate, h->cfg.epilogue != 0, s));
+        const int consumers = step_consumers(h, tokens);
+        ca.r.groups_per_token = h->segs * consumers;
+        rc = hip_status(launch_step(ca, h->cfg.validate, h->cfg.epilogue != 0, consumers, s));
         if (rc) return rc;
         step_enqueued(h, tokens, base);
         return SIFAR_OK;

@@ -14,13 +14,19 @@
 
 namespace sifar {
 
-struct alignas(16) V16 {
-    uint32_t w[4];
+// W words of a lane's payload (2 bf16 a word).
+template <int W>
+struct alignas(4 * W) Words {
+    uint32_t w[W];
 };
+using V16 = Words<4>;
 
-__device__ __forceinline__ V16 ld16(const uint16_t *p) {
-    return *reinterpret_cast<const V16 *>(p);
+template <int W>
+__device__ __forceinline__ Words<W> ld_words(const uint16_t *p) {
+    return *reinterpret_cast<const Words<W> *>(p);
 }
+
+__device__ __forceinline__ V16 ld16(const uint16_t *p) { return ld_words<4>(p); }
 
 // `p`, the same in every lane of the wave, as a value the compiler knows to be
 // wave-uniform (a scalar register pair), as a buffer descriptor needs.
@@ -100,6 +106,18 @@ __device__ __forceinline__ V16 ld16_agent_at(__amdgpu_buffer_rsrc_t rs, uint32_t
     return ld16_at<kCachePolicyAgent>(rs, off, soff);
 }
 
+// W words with ld16_agent_at's addressing and caching.
+template <int W>
+__device__ __forceinline__ Words<W> ld_words_agent_at(__amdgpu_buffer_rsrc_t rs, uint32_t off,
+                                                      uint32_t soff) {
+    static_assert(W == 1 || W == 4, "4 or 16 bytes");
+    if constexpr (W == 4) return ld16_agent_at(rs, off, soff);
+    else
+        return __builtin_bit_cast(
+            Words<1>, __builtin_amdgcn_raw_buffer_load_b32(
+                          rs, static_cast<int>(off), static_cast<int>(soff), kCachePolicyAgent));
+}
+
 // 16 bytes to byte offset off + soff through the descriptor rs (normal
 // caching), made once for several stores.
 __device__ __forceinline__ void st16_at(__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t soff,
@@ -116,18 +134,23 @@ __device__ __forceinline__ void st16_buffer(void *base, uint32_t off, const V16 
     __builtin_amdgcn_raw_buffer_store_b128(x, buffer_rsrc(base), static_cast<int>(off), 0, 0);
 }
 
-__device__ __forceinline__ void st16(uint16_t *p, const V16 &v) {
-    *reinterpret_cast<V16 *>(p) = v;
+template <int W>
+__device__ __forceinline__ void st_words(uint16_t *p, const Words<W> &v) {
+    *reinterpret_cast<Words<W> *>(p) = v;
 }
 
-// A 16-byte store of data no wave of the launch reads again (an all-reduce
+__device__ __forceinline__ void st16(uint16_t *p, const V16 &v) { st_words<4>(p, v); }
+
+// A store of data no wave of the launch reads again (an all-reduce
 // output): non-temporal, so that a large output stream does not push the slots
 // and sources that every epoch re-reads out of the caches.
-__device__ __forceinline__ void st16_stream(uint16_t *p, const V16 &v) {
-    const V4i x = {static_cast<int>(v.w[0]), static_cast<int>(v.w[1]), static_cast<int>(v.w[2]),
-                   static_cast<int>(v.w[3])};
-    __builtin_nontemporal_store(x, reinterpret_cast<V4i *>(p));
+template <int W>
+__device__ __forceinline__ void st_stream(uint16_t *p, const Words<W> &v) {
+    typedef uint32_t VW __attribute__((ext_vector_type(W)));
+    __builtin_nontemporal_store(__builtin_bit_cast(VW, v), reinterpret_cast<VW *>(p));
 }
+
+__device__ __forceinline__ void st16_stream(uint16_t *p, const V16 &v) { st_stream<4>(p, v); }
 
 __device__ __forceinline__ uint32_t ld_relaxed(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -158,8 +181,12 @@ __device__ __forceinline__ void st_release(uint32_t *p, uint32_t v) {
 // Makes every load that fed `v` complete before any later instruction issues:
 // the value is consumed by an (empty) compiler barrier, so the compiler must
 // wait for it there.
-__device__ __forceinline__ void complete(const V16 &v) {
-    asm volatile("" ::"v"(v.w[0]), "v"(v.w[1]), "v"(v.w[2]), "v"(v.w[3]) : "memory");
+template <int W>
+__device__ __forceinline__ void complete(const Words<W> &v) {
+    if constexpr (W == 4)
+        asm volatile("" ::"v"(v.w[0]), "v"(v.w[1]), "v"(v.w[2]), "v"(v.w[3]) : "memory");
+    else
+        asm volatile("" ::"v"(v.w[0]) : "memory");
 }
 
 constexpr uint32_t kPlaceSpins = 1u << 14;  // polls for a partner wave's placement tag

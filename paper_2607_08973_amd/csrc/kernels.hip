@@ -433,25 +433,25 @@ __device__ __forceinline__ bool gather_chain(const ReduceArgs &a, const Chunk &k
 }
 
 // Fixed-order fp32 sum: acc = x_0; acc += x_1; ... acc += x_{N-1}; then bf16.
-template <int N>
-__device__ __forceinline__ V16 sum_round(const V16 (&v)[N]) {
-    float acc[kVec];
+template <int N, int W>
+__device__ __forceinline__ Words<W> sum_round(const Words<W> (&v)[N]) {
+    float acc[2 * W];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
+    for (int k = 0; k < W; ++k) {
         acc[2 * k] = lo_f32(v[0].w[k]);
         acc[2 * k + 1] = hi_f32(v[0].w[k]);
     }
 #pragma unroll
     for (int r = 1; r < N; ++r) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < W; ++k) {
             acc[2 * k] = acc[2 * k] + lo_f32(v[r].w[k]);
             acc[2 * k + 1] = acc[2 * k + 1] + hi_f32(v[r].w[k]);
         }
     }
-    V16 o;
+    Words<W> o;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) o.w[k] = pack_bf16(acc[2 * k], acc[2 * k + 1]);
+    for (int k = 0; k < W; ++k) o.w[k] = pack_bf16(acc[2 * k], acc[2 * k + 1]);
     return o;
 }
 
@@ -647,7 +647,7 @@ __global__ __launch_bounds__(1024) void reduce_kernel(const uint32_t *ep_base, u
     uint32_t attempts, first, last, st_first, st_last;
     const uint32_t g =
         gather<N, MODE, true>(a, k, base_v, p, lane, v, attempts, first, last, st_first, st_last);
-    const V16 o = sum_round<N>(v);
+    const V16 o = sum_round<N, 4>(v);
     if (k.active && lane == 0) {
         write_log(a, k, g, log_word(attempts, first, last));
         a.consumed[static_cast<size_t>(p) * geo.w_max + k.c] = g;
@@ -673,19 +673,20 @@ __global__ __launch_bounds__(1024) void reduce_kernel(const uint32_t *ep_base, u
 // residual_rmsnorm's. Four planes suffice: a group can publish epoch g + 4
 // only after finishing epoch g + 2, which needs every group's word of g + 2,
 // and a group publishes that only after it finished epoch g.
+template <int W>
 struct EpiPending {
-    V16 res;    // res' of this lane's 8 elements
+    Words<W> res;  // res' of this lane's elements
     float grp;  // this workgroup's sum of squares
     uint32_t g; // the epoch
 };
 
-template <bool GROUPED>
+template <bool GROUPED, int W>
 __device__ __forceinline__ void epi_stage(const ReduceArgs &a, const Chunk &k, uint32_t g,
-                                          const V16 &o, V16 &res, int lane, int wave, int G,
-                                          int q, bool xlocal, EpiPending &pd) {
+                                          const Words<W> &o, Words<W> &res, int lane, int wave,
+                                          int G, int q, bool xlocal, EpiPending<W> &pd) {
     float ss = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < W; ++i) {
         const float a0 = lo_f32(o.w[i]), a1 = hi_f32(o.w[i]);
         res.w[i] = pack_bf16(a0 + lo_f32(res.w[i]), a1 + hi_f32(res.w[i]));
         const float x0 = lo_f32(res.w[i]), x1 = hi_f32(res.w[i]);
@@ -735,10 +736,10 @@ __device__ __forceinline__ uint64_t epi_word(const ReduceArgs &a, const Chunk &k
 // compiler kept the pending state in scratch memory.) True in wave 0 when the
 // exchange wait failed: it ran out of polls (latched here), or found an error
 // latched elsewhere.
-template <bool GROUPED>
+template <bool GROUPED, int W>
 __device__ __forceinline__ bool epi_finish(const ReduceArgs &a, const Chunk &k,
-                                           const EpiPending pd, uint64_t mine, const V16 &wv,
-                                           uint16_t *y, int lane, int wave) {
+                                           const EpiPending<W> pd, uint64_t mine,
+                                           const Words<W> &wv, uint16_t *y, int lane, int wave) {
     const int Q = a.groups_per_token;
     float tot = pd.grp;
     bool failed = false;
@@ -764,13 +765,13 @@ __device__ __forceinline__ bool epi_finish(const ReduceArgs &a, const Chunk &k,
         }
     }
     const float inv = 1.0f / __builtin_sqrtf(tot / static_cast<float>(a.geo.hidden) + a.eps);
-    V16 yo;
+    Words<W> yo;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < W; ++i) {
         const float w0 = lo_f32(wv.w[i]), w1 = hi_f32(wv.w[i]);
         yo.w[i] = pack_bf16((lo_f32(pd.res.w[i]) * inv) * w0, (hi_f32(pd.res.w[i]) * inv) * w1);
     }
-    if (k.lane_ok) st16(y + k.row, yo);
+    if (k.lane_ok) st_words<W>(y + k.row, yo);
     return failed;
 }
 
@@ -970,7 +971,7 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
         wv = ld16(a.weight + k.elem);
         res = ld16(a.residual + k.row);
     }
-    EpiPending pending;   // the epilogue of the previous epoch, finished one epoch late
+    EpiPending<4> pending;  // the epilogue of the previous epoch, finished one epoch late
     bool have_pending = false;
     // Every lane polls a stamp of this chunk (lanes >= N repeat rank N - 1's,
     // which the ballot ignores), so no branch surrounds the poll.
@@ -1016,7 +1017,7 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
             for (int r = 0; r < N; ++r) complete(v[r]);
             poll_next_and_release();
         }
-        const V16 o = sum_round<N>(v);
+        const V16 o = sum_round<N, 4>(v);
         if (EPI) {
             complete(o);  // every payload load has returned before the slot is released
             poll_next_and_release();
@@ -1031,9 +1032,9 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
             // so they store the same bytes to the same place: no branch.
             st16_stream(a.out + ring + k.row, o);
         } else {
-            EpiPending cur;
-            epi_stage<GROUPED>(a, k, g, o, res, lane, wave, G, bx, xlocal, cur);
-            if (have_pending && epi_finish<GROUPED>(a, k, pending, word, wv,
+            EpiPending<4> cur;
+            epi_stage<GROUPED, 4>(a, k, g, o, res, lane, wave, G, bx, xlocal, cur);
+            if (have_pending && epi_finish<GROUPED, 4>(a, k, pending, word, wv,
                                                     a.y + ring - A.ring_stride, lane, wave))
                 stop = true;
             pending = cur;
@@ -1055,7 +1056,7 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
     if (EPI) {
         if (k.lane_ok) st16(a.residual + k.row, res);
         const uint64_t word = wave == 0 ? epi_word(a, k, pending.g, lane) : 0;
-        epi_finish<GROUPED>(a, k, pending, word, wv,
+        epi_finish<GROUPED, 4>(a, k, pending, word, wv,
                             a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane, wave);
     }
 }
@@ -1120,8 +1121,8 @@ __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
 // Per-epoch step in one launch: every all-reduce of a decode step, with a
 // workgroup barrier where the step graph has a launch boundary.
 //
-// A workgroup is one chunk: wave 0 is its consumer, wave 1 plays its peers.
-// Phase i: the peers write epoch base + i + 1 while the consumer reduces epoch
+// A workgroup is one chunk: its first wave (or first four, a quarter of the
+// chunk's elements each) is the consumer, its last plays the peers. Phase i: the peers write epoch base + i + 1 while the consumer reduces epoch
 // base + i; the barrier between phases orders them as the end of a launch
 // would, so speculation is as exact here as there: whatever the consumer loads
 // in a phase was written before the barrier. Chunks share nothing, so no
@@ -1144,6 +1145,19 @@ __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
 // their whole step one after another, which no sequence of all-reduces does.
 // INJECT: the kernel that knows the injection table; without one the table's
 // branches leave the scalar registers (and 5 % of the time).
+//
+// Four consumer waves: the sum is ~130 vector instructions of a wave, 0.2 us,
+// of which the payload's arrival covers a fourth; split four ways it is nearly
+// hidden. No wave waits for a partner's poll here (the barrier is there
+// anyway), which is what makes the split pay. Measured, one -> four (64
+// all-reduces, us per all-reduce): N = 8, 8 chunks 0.573 -> 0.517, 128 chunks
+// 0.601 -> 0.533, 256 chunks 0.644 -> 0.576; N = 4, 64 chunks 0.455 -> 0.420;
+// N = 2, 64 chunks 0.396 -> 0.390; with the epilogue 128 chunks 1.03 -> 0.90.
+// At 512 chunks it is 0.803 -> 0.740 (N = 8, rows of 4096) but 0.99 -> 1.01
+// (N = 5, ragged rows of 3896), at 1024 2.75 -> 2.74. (Two waves were slower
+// than one at N = 4 and 8: 0.58 -> 0.63.) So steps split up to 256 chunks, one
+// per CU; epilogue steps no further than a quarter of the places of the wider
+// workgroup.
 
 // Phase boundary: orders the two waves' memory operations on their CU.
 __device__ __forceinline__ void phase_barrier() {
@@ -1158,9 +1172,9 @@ __device__ __forceinline__ void phase_barrier() {
 // each addressed through one descriptor, every rank at a scalar offset (the
 // host checks that they fit 31 bits): pointers per rank overflow the scalar
 // registers.
-template <int N, bool INJECT>
+template <int N, bool INJECT, int C>
 __device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base, const Chunk &k,
-                                              int lane, uint32_t (&done)[2]) {
+                                              int lane, uint32_t (&done)[2][C]) {
     const ProduceArgs &a = A.p;
     const Geometry &geo = a.geo;
     const uint32_t off = lane_offset(geo, k);
@@ -1195,9 +1209,9 @@ __device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base,
         const size_t pc = static_cast<size_t>(p) * geo.w_max + k.c;
         const uint64_t at = static_cast<uint64_t>(p) * geo.slot_elems + first;
         if (i >= 2) {
-            const uint32_t fin =
-                __hip_atomic_load(&done[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (lane == 0 && fin != g - 2u) latch(a.err, kErrWaw, g, k.c, g - 2u);
+            const uint32_t fin = __hip_atomic_load(&done[p][lane % C], __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (lane < C && fin != g - 2u) latch(a.err, kErrWaw, g, k.c, g - 2u);
         }
         const uint32_t inj = INJECT ? __builtin_amdgcn_readfirstlane(word) : 0u;
         const uint32_t staged = late_ranks(inj);
@@ -1249,24 +1263,40 @@ __device__ __forceinline__ void catch_up(const ReduceArgs &a, const Chunk &k, ui
     if (lane < N && ((late >> lane) & 1u)) st_flag(stamp + lane, g, true);
 }
 
-template <int N, int MODE, bool EPI, bool INJECT>
-__device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base, const Chunk &k,
-                                              int lane, uint32_t (&done)[2]) {
+// Where lane `lane` of consumer wave w of C works: its 8 / C elements of the
+// chunk, as chunk_at places them for one wave.
+template <int C>
+__device__ __forceinline__ Chunk part_of(const Geometry &geo, Chunk k, int w, int lane) {
+    const int raw = k.s * kChunk + w * (kChunk / C) + lane * (kVec / C);
+    k.lane_ok = raw < geo.hidden;
+    k.elem = k.lane_ok ? raw : geo.hidden - kVec / C;
+    k.row = static_cast<uint64_t>(k.t) * geo.hidden + k.elem;
+    return k;
+}
+
+// Consumer wave w of C. Each validates its part's stamps itself; wave 0 keeps the
+// log (without injection no stamp is ever stale, so the waves cannot differ).
+template <int N, int MODE, bool EPI, bool INJECT, int C>
+__device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base, const Chunk &kc,
+                                              int w, int lane, uint32_t (&done)[2][C]) {
+    static_assert(!INJECT || C == 1, "late ranks catch up in one consumer wave");
+    constexpr int W = 4 / C;
     const ReduceArgs &a = A.r;
     const Geometry &geo = a.geo;
+    const Chunk k = part_of<C>(geo, kc, w, lane);
     const uint32_t off = lane_offset(geo, k);
     const uint32_t rank_bytes = static_cast<uint32_t>(geo.slot_elems) * 4u;
     // the epilogue as in the persistent step: finished one epoch late
     bool xlocal = false;
-    V16 wv, res;
-    EpiPending pending;
+    Words<W> wv, res;
+    EpiPending<W> pending;
     if (EPI) {
-        publish_place(A.place + k.c, base, lane);
+        if (w == 0) publish_place(A.place + k.c, base, lane);
         xlocal = __ballot(lane < geo.segs &&
                           !tag_is_local(A.place + static_cast<size_t>(k.t) * geo.segs + lane,
                                         base)) == 0;
-        wv = ld16(a.weight + k.elem);
-        res = ld16(a.residual + k.row);
+        wv = ld_words<W>(a.weight + k.elem);
+        res = ld_words<W>(a.residual + k.row);
     }
     for (int i = 0; i < A.reduces; ++i) {
         const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
@@ -1276,15 +1306,15 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
             a.slots + static_cast<uint64_t>(p) * geo.slot_elems + chunk_first(geo, k));
         uint32_t *stamp = a.stamps + pc * N;
         const uint32_t *stamp_lane = stamp + (lane < N ? lane : N - 1);
-        auto load = [&](V16(&v)[N]) {
+        auto load = [&](Words<W>(&v)[N]) {
 #pragma unroll
             for (int r = 0; r < N; ++r)
-                v[r] = ld16_agent_at(rs, off, static_cast<uint32_t>(r) * rank_bytes);
+                v[r] = ld_words_agent_at<W>(rs, off, static_cast<uint32_t>(r) * rank_bytes);
         };
         phase_barrier();
         uint64_t word = 0;  // the previous epoch's exchange word
         if (EPI && i > 0) word = epi_word(a, k, pending.g, lane);
-        V16 v[N];
+        Words<W> v[N];
         uint32_t st = 0, attempts = 1, first = 0, last = 0;
         uint32_t inj = 0;
         if (INJECT) inj = inject_word(a.inject, a.inject_div, g);
@@ -1292,8 +1322,8 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
         if (MODE != kNone) st = ld_relaxed(stamp_lane);
         // speculative: the sum runs as the payload arrives, the stamps decide
         // afterwards whether it stands
-        V16 o;
-        if (MODE != kOrdered) o = sum_round<N>(v);
+        Words<W> o;
+        if (MODE != kOrdered) o = sum_round<N, W>(v);
         const uint32_t st_first = st;
         if (MODE != kNone) {
             uint32_t m = static_cast<uint32_t>(__ballot(lane < N && st != g));
@@ -1314,47 +1344,50 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
                 m = static_cast<uint32_t>(__ballot(lane < N && st != g));
                 last = m;
                 fail = m != 0 || attempts <= a.forced_retries;
-                if (MODE != kOrdered && !fail) o = sum_round<N>(v);
+                if (MODE != kOrdered && !fail) o = sum_round<N, W>(v);
             }
         }
         if (MODE == kOrdered) {
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
             load(v);
-            o = sum_round<N>(v);
+            o = sum_round<N, W>(v);
         }
         complete(o);  // every payload load has returned: the slot is free
         if (lane == 0)
-            __hip_atomic_store(&done[p], g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        write_log(a, k, g, log_word(attempts, first, last));
-        write_stamp_log<N>(a, k, g, lane < N ? lane : N - 1, st_first, st);
-        st_flag(a.consumed + pc, g, true);
+            __hip_atomic_store(&done[p][w], g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (C == 1 || w == 0) {
+            write_log(a, k, g, log_word(attempts, first, last));
+            write_stamp_log<N>(a, k, g, lane < N ? lane : N - 1, st_first, st);
+            st_flag(a.consumed + pc, g, true);
+        }
         const uint64_t ring = static_cast<uint64_t>(i) * A.ring_stride;
         if (!EPI) {
             // lanes past the row's end store the owning lane's bytes again
-            st16_stream(a.out + ring + k.row, o);
+            st_stream<W>(a.out + ring + k.row, o);
         } else {
-            EpiPending cur;
-            epi_stage<false>(a, k, g, o, res, lane, 0, 1, k.s, xlocal, cur);
+            EpiPending<W> cur;
+            epi_stage<false, W>(a, k, g, o, res, lane, 0, 1, k.s * C + w, xlocal, cur);
             if (i > 0)
-                epi_finish<false>(a, k, pending, word, wv, a.y + ring - A.ring_stride, lane, 0);
+                epi_finish<false, W>(a, k, pending, word, wv, a.y + ring - A.ring_stride, lane, 0);
             pending = cur;
         }
     }
     if (EPI) {
-        if (k.lane_ok) st16(a.residual + k.row, res);
-        epi_finish<false>(a, k, pending, epi_word(a, k, pending.g, lane), wv,
+        if (k.lane_ok) st_words<W>(a.residual + k.row, res);
+        epi_finish<false, W>(a, k, pending, epi_word(a, k, pending.g, lane), wv,
                           a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane, 0);
     }
 }
 
-// Grid (segs, tokens), two waves; with the epilogue (8 * ceil(tokens / 8) *
-// segs) with every workgroup of a token on one XCD, as in chain_kernel
-// (workgroups past the last token only arrive on the counter). The last workgroup to arrive on the counter
-// advances the epoch base for the next step: both waves of every workgroup
-// read it before their first barrier.
-template <int N, int MODE, bool EPI, bool INJECT>
-__global__ __launch_bounds__(2 * kLanes, EPI ? 5 : 8) void step_kernel(ChainArgs A) {
-    __shared__ uint32_t done[2];
+// Grid (segs, tokens), C consumer waves and one producer wave; with the
+// epilogue (8 * ceil(tokens / 8) * segs) with every workgroup of a token on one
+// XCD, as in chain_kernel (workgroups past the last token only arrive on the
+// counter). The last workgroup to arrive on the counter advances the epoch base
+// for the next step: every wave of a workgroup read it before its first
+// barrier.
+template <int N, int MODE, bool EPI, bool INJECT, int C>
+__global__ __launch_bounds__((C + 1) * kLanes, EPI ? 5 : 8) void step_kernel(ChainArgs A) {
+    __shared__ uint32_t done[2][C];
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kLanes);
     const uint32_t base = A.r.ep.base[0];
@@ -1366,15 +1399,13 @@ __global__ __launch_bounds__(2 * kLanes, EPI ? 5 : 8) void step_kernel(ChainArgs
     }
     if (!EPI || by < A.r.geo.tokens) {
         const Chunk k = chunk_at(A.r.geo, by, bx, lane);
-        if (wave == 1) {
-            step_producer<N, INJECT>(A, base, k, lane, done);
+        if (wave == C) {
+            step_producer<N, INJECT, C>(A, base, k, lane, done);
             return;
         }
-        step_consumer<N, MODE, EPI, INJECT>(A, base, k, lane, done);
-    } else if (wave == 1) {
-        return;
+        step_consumer<N, MODE, EPI, INJECT, C>(A, base, k, wave, lane, done);
     }
-    if (lane == 0) {
+    if (threadIdx.x == 0) {
         const uint32_t before =
             __hip_atomic_fetch_add(A.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (before == gridDim.x * gridDim.y - 1u) {
@@ -1437,7 +1468,7 @@ __global__ __launch_bounds__(2 * kLanes, 8) void once_kernel(const uint16_t *src
         for (int r = 0; r < N; ++r)
             v[r] = ld16_agent_at(rs, off, static_cast<uint32_t>(r) * rank_bytes);
         const uint32_t st = ld_relaxed(stamp + (lane < N ? lane : N - 1));
-        o = sum_round<N>(v);
+        o = sum_round<N, 4>(v);
         m = static_cast<uint32_t>(__ballot(lane < N && st != g));
         if (attempts++ == 0) first = m;
         // a stale stamp can only come from a call that overlaps this one
@@ -1553,39 +1584,49 @@ const void *chain_fn_any(int nranks, int mode, bool epi, bool grouped, bool pref
     return nullptr;
 }
 
-// `inject`: the kernel that knows the injection table and the stage. NONE
-// validates nothing, so it has no injection.
-template <int N, int MODE>
-const void *step_fn(bool epi, bool inject) {
-    if (!inject)
-        return epi ? reinterpret_cast<const void *>(step_kernel<N, MODE, true, false>)
-                   : reinterpret_cast<const void *>(step_kernel<N, MODE, false, false>);
-    if (MODE == kNone) return nullptr;
-    constexpr int M = MODE == kNone ? kSpec : MODE;
-    return epi ? reinterpret_cast<const void *>(step_kernel<N, M, true, true>)
-               : reinterpret_cast<const void *>(step_kernel<N, M, false, true>);
-}
-
-template <int N>
-const void *step_fn_n(int mode, bool epi, bool inject) {
-    switch (mode) {
-        case kSpec: return step_fn<N, kSpec>(epi, inject);
-        case kOrdered: return step_fn<N, kOrdered>(epi, inject);
-        case kNone: return step_fn<N, kNone>(epi, inject);
+// `inject`: the kernel that knows the injection table and the stage (one
+// consumer wave). NONE validates nothing, so it has no injection.
+template <int N, int MODE, bool EPI>
+const void *step_fn(bool inject, int consumers) {
+    if (inject) {
+        if (MODE == kNone || consumers != 1) return nullptr;
+        return reinterpret_cast<const void *>(
+            step_kernel<N, MODE == kNone ? kSpec : MODE, EPI, true, 1>);
+    }
+    switch (consumers) {
+        case 1: return reinterpret_cast<const void *>(step_kernel<N, MODE, EPI, false, 1>);
+        case kStepConsumers:
+            return reinterpret_cast<const void *>(step_kernel<N, MODE, EPI, false, kStepConsumers>);
     }
     return nullptr;
 }
 
-const void *step_fn_any(int nranks, int mode, bool epi, bool inject) {
+template <int N>
+const void *step_fn_n(int mode, bool epi, bool inject, int consumers) {
+    switch (mode) {
+        case kSpec:
+            return epi ? step_fn<N, kSpec, true>(inject, consumers)
+                       : step_fn<N, kSpec, false>(inject, consumers);
+        case kOrdered:
+            return epi ? step_fn<N, kOrdered, true>(inject, consumers)
+                       : step_fn<N, kOrdered, false>(inject, consumers);
+        case kNone:
+            return epi ? step_fn<N, kNone, true>(inject, consumers)
+                       : step_fn<N, kNone, false>(inject, consumers);
+    }
+    return nullptr;
+}
+
+const void *step_fn_any(int nranks, int mode, bool epi, bool inject, int consumers) {
     switch (nranks) {
-        case 1: return step_fn_n<1>(mode, epi, inject);
-        case 2: return step_fn_n<2>(mode, epi, inject);
-        case 3: return step_fn_n<3>(mode, epi, inject);
-        case 4: return step_fn_n<4>(mode, epi, inject);
-        case 5: return step_fn_n<5>(mode, epi, inject);
-        case 6: return step_fn_n<6>(mode, epi, inject);
-        case 7: return step_fn_n<7>(mode, epi, inject);
-        case 8: return step_fn_n<8>(mode, epi, inject);
+        case 1: return step_fn_n<1>(mode, epi, inject, consumers);
+        case 2: return step_fn_n<2>(mode, epi, inject, consumers);
+        case 3: return step_fn_n<3>(mode, epi, inject, consumers);
+        case 4: return step_fn_n<4>(mode, epi, inject, consumers);
+        case 5: return step_fn_n<5>(mode, epi, inject, consumers);
+        case 6: return step_fn_n<6>(mode, epi, inject, consumers);
+        case 7: return step_fn_n<7>(mode, epi, inject, consumers);
+        case 8: return step_fn_n<8>(mode, epi, inject, consumers);
     }
     return nullptr;
 }
@@ -1717,11 +1758,14 @@ hipError_t launch_once(const Geometry &geo, uint32_t g, const uint16_t *src, int
     return hipGetLastError();
 }
 
-hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, hipStream_t s) {
-    const void *fn = step_fn_any(a.r.geo.nranks, mode, epilogue, a.p.stage != nullptr);
-    if (epilogue && (a.r.geo.segs > kLanes || a.r.groups_per_token != a.r.geo.segs))
+hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, int consumers,
+                       hipStream_t s) {
+    const void *fn = step_fn_any(a.r.geo.nranks, mode, epilogue, a.p.stage != nullptr, consumers);
+    if (epilogue && (a.r.geo.segs * consumers > kLanes ||
+                     a.r.groups_per_token != a.r.geo.segs * consumers))
         return hipErrorInvalidValue;
-    if (!fn || a.parity_mask != 1u || !a.r.stamp_log || (a.p.inject && !a.p.stage)) return hipErrorInvalidValue;
+    if (!fn || a.parity_mask != 1u || !a.r.stamp_log || (a.p.inject && !a.p.stage))
+        return hipErrorInvalidValue;
     // slots and sources are addressed at 32-bit offsets from rank 0's
     if (!step_offsets_fit(a.r.geo.nranks, a.r.geo.slot_elems) ||
         !source_offsets_fit(a.r.geo.nranks, a.p.rank_stride))
@@ -1730,12 +1774,17 @@ hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, hipStream_t 
     const uint32_t tokens = static_cast<uint32_t>(a.r.geo.tokens);
     const dim3 grid = epilogue ? dim3((tokens + 7u) / 8u * 8u * segs) : dim3(segs, tokens);
     void *args[] = {const_cast<ChainArgs *>(&a)};
-    return hipLaunchKernel(fn, grid, dim3(2 * kLanes), args, 0, s);
+    return hipLaunchKernel(fn, grid, dim3((consumers + 1) * kLanes), args, 0, s);
+}
+
+int max_active_split_step_groups(int nranks, int mode, bool epilogue) {
+    return resident_groups(step_fn_any(nranks, mode, epilogue, false, kStepConsumers),
+                           (kStepConsumers + 1) * kLanes);
 }
 
 int max_active_step_groups(int nranks, int mode, bool epilogue) {
-    const int lean = resident_groups(step_fn_any(nranks, mode, epilogue, false), 2 * kLanes);
-    const void *fn = step_fn_any(nranks, mode, epilogue, true);
+    const int lean = resident_groups(step_fn_any(nranks, mode, epilogue, false, 1), 2 * kLanes);
+    const void *fn = step_fn_any(nranks, mode, epilogue, true, 1);
     const int full = fn ? resident_groups(fn, 2 * kLanes) : lean;
     return full < lean ? full : lean;
 }

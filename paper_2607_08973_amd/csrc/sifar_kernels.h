@@ -13,6 +13,8 @@ constexpr int kChunk = kLanes * kVec;      // elements per chunk: one wave, one 
 constexpr int kMaxRanks = 8;
 constexpr int kMaxWavesPerGroup = 16;
 constexpr int kChainGroupWaves = 4;         // waves per persistent-step workgroup when grouped
+constexpr int kStepConsumers = 4;           // consumer waves of a one-launch step's chunk when split
+constexpr int kSplitChunks = 256;           // most chunks of a step that splits them
 constexpr int kExchPlanes = 4;              // epoch-indexed planes of the epilogue exchange
 
 // x % d for a divisor fixed per launch, by a multiply-high instead of a
@@ -193,10 +195,14 @@ inline bool source_offsets_fit(int nranks, int64_t rank_stride) {
 // All-reduce of epoch g in one launch, a two-wave workgroup per chunk.
 hipError_t launch_once(const Geometry &geo, uint32_t g, const uint16_t *src, int64_t rank_stride,
                        uint16_t *slots, uint32_t *stamps, const OnceArgs &a, hipStream_t s);
-// Per-epoch step in one launch (dual buffers): a two-wave workgroup per chunk,
-// and how many of them can be resident at once.
-hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, hipStream_t s);
+// Per-epoch step in one launch (dual buffers): a workgroup per chunk, of
+// `consumers` (1, or without an injection table kStepConsumers) reducing waves
+// and one of the peers; how many workgroups with one, and with kStepConsumers,
+// can be resident at once.
+hipError_t launch_step(const ChainArgs &a, int mode, bool epilogue, int consumers,
+                       hipStream_t s);
 int max_active_step_groups(int nranks, int mode, bool epilogue);
+int max_active_split_step_groups(int nranks, int mode, bool epilogue);
 hipError_t launch_advance(uint32_t *epoch_base, uint32_t step, hipStream_t s);
 hipError_t launch_set_base(uint32_t *epoch_base, uint32_t value, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t *p, uint32_t value, uint64_t count, hipStream_t s);

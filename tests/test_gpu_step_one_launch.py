@@ -33,9 +33,11 @@ def _same_words(a, b, T, epochs):
 
 
 # the smallest row, a row of one full and one 8-element chunk, ragged rows,
-# many chunks; chain lengths of 1, 2 and odd; every rank count's ends
+# many chunks; both sides of 256 chunks (four consumer waves per chunk, or one);
+# chain lengths of 1, 2 and odd; every rank count's ends
 @pytest.mark.parametrize("mode", ["spec", "ordered", "none"])
-@pytest.mark.parametrize("N,T,H,L,G", [(1, 1, 8, 1, 1), (8, 3, 520, 2, 2), (5, 7, 3896, 5, 16),
+@pytest.mark.parametrize("N,T,H,L,G", [(4, 32, 4096, 3, 1), (4, 257, 504, 3, 1), (6, 37, 3592, 3, 2),
+                                       (1, 1, 8, 1, 1), (8, 3, 520, 2, 2), (5, 7, 3896, 5, 16),
                                        (2, 9, 4608, 7, 4), (8, 64, 4096, 4, 1),
                                        (3, 130, 8192, 3, 8)])
 def test_one_launch_equals_separate_launches(N, T, H, L, G, mode):
@@ -122,7 +124,9 @@ def test_withheld_stamp_in_one_launch_latches():
     r.s.close()
 
 
-@pytest.mark.parametrize("N,T,H,L,G,p", [(8, 3, 8192, 6, 1, 0.3), (5, 9, 1000, 5, 2, 0.1),
+@pytest.mark.parametrize("N,T,H,L,G,p", [(8, 2, 4104, 5, 1, 0.0), (3, 16, 8192, 4, 2, 0.0),
+                                         (4, 17, 8192, 3, 2, 0.0), (7, 5, 3592, 4, 1, 0.0),
+                                         (8, 3, 8192, 6, 1, 0.3), (5, 9, 1000, 5, 2, 0.1),
                                          (1, 1, 520, 1, 1, 0.0), (2, 40, 8192, 3, 4, 0.1)])
 @pytest.mark.parametrize("mode", ["spec", "ordered"])
 def test_epilogue_one_launch_equals_separate_launches(N, T, H, L, G, p, mode):
@@ -196,4 +200,26 @@ def test_epilogue_steps_of_four_handles_at_once():
     for r in runs:
         r.s.check()
         assert np.array_equal(to_host(r.res_d), res)
+        r.s.close()
+
+
+@pytest.mark.parametrize("epilogue", [False, True])
+def test_forced_retries_without_a_table(epilogue):
+    """Every validation repeated twice, in steps whose chunks have four consumer
+    waves: each wave repeats its own, the log counts three."""
+    N, T, H, L = 8, 2, 1000, 5
+    w = synth.Workload(94, "one-launch-forced", N, (T,), H, L, 1, "act", epilogue=epilogue)
+    a = StepRun(w, T, forced_retries=2)
+    b = StepRun(w, T, forced_retries=2, fuse_peers=0, pool=a.pool)
+    for step in range(2):
+        ea, eb = a.step(T), b.step(T)
+        assert ea == eb
+        _same_words(a, b, T, ea)
+        assert np.all((a.s.read_log()[:L, :4] & 0xFFFF) == 3)
+        if epilogue:
+            assert np.array_equal(to_host(a.res_d), to_host(b.res_d))
+        else:
+            assert np.array_equal(to_host(a.out_d), to_host(b.out_d))
+    for r in (a, b):
+        r.s.check()
         r.s.close()
