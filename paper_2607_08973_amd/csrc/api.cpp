@@ -31,9 +31,9 @@ struct sifar_ctx {
     uint32_t *log = nullptr;       // [log_epochs][w_max]
     uint32_t *stamp_log = nullptr; // [log_epochs][w_max][2][N]
     uint16_t *stage = nullptr;     // [N][2][slot_elems]: late ranks' payload (deterministic injection)
-    uint64_t *exch = nullptr;      // [kExchPlanes][max_tokens][exch_q]
+    uint64_t *exch = nullptr;      // [kExchPlanes][exch_words]
     uint64_t *place = nullptr;     // [2][w_max] XCD tags of each chunk's consumer / producer
-    int exch_q = 1;                // exchange words per token and parity
+    int exch_words = 1;            // exchange words per plane
     DevState *state = nullptr;
     uint16_t *inject = nullptr;
     int32_t inject_entries = 0;
@@ -157,7 +157,7 @@ ReduceArgs reduce_args(const sifar_t h, int32_t tokens, EpochRef ep) {
     a.stage = h->inject ? h->stage : nullptr;
     a.exch = h->exch;
     a.groups_per_token = h->groups_per_token;
-    a.exch_parity_stride = h->cfg.max_tokens * h->exch_q;
+    a.exch_parity_stride = h->exch_words;
     a.eps = h->cfg.rms_eps;
     a.err = h->state->err;
     return a;
@@ -365,7 +365,9 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
             }
         }
     }
-    h->exch_q = c.persistent && h->segs > h->groups_per_token ? h->segs : h->groups_per_token;
+    h->exch_words = c.max_tokens * (c.persistent && h->segs > h->groups_per_token
+                                        ? h->segs
+                                        : h->groups_per_token);
     if (c.persistent) {
         // every consumer and producer wave of a step is resident at once;
         // with the epilogue the grid pads the tokens to a multiple of 8 (one
@@ -402,7 +404,9 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
         if (c.epilogue) {
             h->step_cap /= 4;
             h->split_cap /= 4;
-            h->exch_q = kLanes;  // a word for each of a token's consumer waves
+            // a word for each consumer wave of the largest one-launch step
+            const int words = h->step_cap * kStepConsumers;
+            if (h->exch_words < words) h->exch_words = words;
         }
         if (h->split_cap > kSplitChunks) h->split_cap = kSplitChunks;
     }
@@ -415,7 +419,7 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
     if (!rc)
         rc = dev_alloc(&h->stamp_log,
                        static_cast<size_t>(c.log_epochs) * h->w_max * 2 * c.nranks);
-    if (!rc) rc = dev_alloc(&h->exch, static_cast<size_t>(kExchPlanes) * c.max_tokens * h->exch_q);
+    if (!rc) rc = dev_alloc(&h->exch, static_cast<size_t>(kExchPlanes) * h->exch_words);
     if (!rc) rc = dev_alloc(&h->place, static_cast<size_t>(2) * h->w_max);
     if (!rc) rc = dev_alloc(&h->state, 1);
     if (!rc && hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking) != hipSuccess)
@@ -435,7 +439,7 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
                                 static_cast<uint64_t>(c.log_epochs) * h->w_max * 2 * c.nranks, s);
         if (e == hipSuccess)
             e = launch_fill_u32(reinterpret_cast<uint32_t *>(h->exch), 0,
-                                static_cast<uint64_t>(kExchPlanes) * c.max_tokens * h->exch_q * 2,
+                                static_cast<uint64_t>(kExchPlanes) * h->exch_words * 2,
                                 s);
         if (e == hipSuccess)
             e = launch_fill_u32(reinterpret_cast<uint32_t *>(h->place), 0,

@@ -129,11 +129,12 @@ struct ReduceArgs {
     uint16_t *residual;          // epilogue: [tokens][hidden], in place
     const uint16_t *weight;      // [hidden]
     uint16_t *y;                 // [tokens][hidden]
-    uint64_t *exch;              // [kExchPlanes][max_tokens][groups_per_token]: (epoch << 32) |
-                                 // partial bits; per-launch epilogues use planes g & 1,
+    uint64_t *exch;              // [kExchPlanes][words]: token t's word of group q at
+                                 // t * groups_per_token + q: (epoch << 32) | partial bits;
+                                 // per-launch epilogues use planes g & 1, one-launch and
                                  // persistent steps g mod kExchPlanes
     int32_t groups_per_token;
-    int32_t exch_parity_stride;  // max_tokens * groups_per_token
+    int32_t exch_parity_stride;  // words per exchange plane
     float eps;
     uint32_t *err;
 };
