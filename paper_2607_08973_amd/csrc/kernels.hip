@@ -1122,21 +1122,22 @@ __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
 // workgroup barrier where the step graph has a launch boundary.
 //
 // A workgroup is one chunk: its first wave (or first four, a quarter of the
-// chunk's elements each) is the consumer, its last plays the peers. Phase i: the peers write epoch base + i + 1 while the consumer reduces epoch
-// base + i; the barrier between phases orders them as the end of a launch
-// would, so speculation is as exact here as there: whatever the consumer loads
-// in a phase was written before the barrier. Chunks share nothing, so no
-// workgroup waits for another. Barrier and loads stay on one CU: the peers'
-// stores need no acknowledgement and no release fence before the barrier, the
-// consumer's loads follow them through the CU's memory pipeline and are served
-// by the XCD's L2 (agent scope: past the L1).
+// chunk's elements each) is the consumer, its last plays the peers. Phase i:
+// the peers write epoch base + i + 1 while the consumer reduces epoch base +
+// i; the barrier between phases orders them as the end of a launch would, so
+// speculation is as exact here as there: whatever the consumer loads in a
+// phase was written before the barrier. Chunks share nothing, so no workgroup
+// waits for another. Barrier and loads stay on one CU: the peers' stores need
+// no acknowledgement and no release fence before the barrier, the consumer's
+// loads follow them through the CU's memory pipeline and are served by the
+// XCD's L2 (agent scope: past the L1).
 //
 // What bounds it: the consumer's phase, one L2 round trip (payload and stamps
 // together), the rest of the sum that the loads' arrival does not cover, and
 // the issue of its stores; from 1024 chunks at N = 8 the bytes. Measured
 // against one launch per all-reduce (us per all-reduce, launches -> one
-// launch): N = 8, 4 tokens x 4096, 64 per step, 2.62 -> 0.58; with 10 % late
-// stamps 3.70 -> 1.20; 20 per step: N = 2, 1 x 4096, 2.59 -> 0.49; N = 8, 64 x
+// launch, one consumer wave): N = 8, 4 tokens x 4096, 64 per step, 2.62 ->
+// 0.58; with 10 % late stamps 3.70 -> 1.16; 20 per step: N = 2, 1 x 4096, 2.59 -> 0.49; N = 8, 64 x
 // 4096, 3.69 -> 1.14; 64 x 8192, 5.49 -> 3.04; 256 x 8192 (4096 chunks, every
 // wave slot of the GPU), 16.3 -> 14.0; N = 2, 256 x 8192, 6.46 -> 3.92. With
 // the epilogue: 1 x 4096, 4.57 -> 1.13; 40 x 8192, 7.21 -> 1.71; 32 x 8192 with
@@ -1159,7 +1160,7 @@ __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
 // per CU; epilogue steps no further than a quarter of the places of the wider
 // workgroup.
 
-// Phase boundary: orders the two waves' memory operations on their CU.
+// Phase boundary: orders the workgroup's memory operations on their CU.
 __device__ __forceinline__ void phase_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_barrier();
