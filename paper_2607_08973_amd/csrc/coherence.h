@@ -53,12 +53,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void *base) 
                                              kBufferWord3);
 }
 
-// ... of no bytes unless `on` (wave-uniform): loads through it return 0 and
-// stores are dropped by the bounds check, so a choice per rank needs no branch
-// (a branch would make the accesses on its far side wait for those before it).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc_if(const void *base, bool on) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(uniform_ptr(base)), 0,
-                                             on ? 0x7fffffff : 0, kBufferWord3);
+// A lane's byte offset, or one past every descriptor's range unless `on`
+// (wave-uniform): loads there return 0 and stores are dropped by the bounds
+// check, so a choice per rank needs no branch (a branch would make the accesses
+// on its far side wait for those before it) and no descriptor of its own.
+__device__ __forceinline__ uint32_t offset_if(uint32_t off, bool on) {
+    return on ? off : 0x80000000u;
 }
 
 typedef int V4i __attribute__((ext_vector_type(4)));

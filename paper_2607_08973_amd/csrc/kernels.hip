@@ -1172,7 +1172,9 @@ __device__ __forceinline__ void phase_barrier() {
 // the words that earlier launches left in memory. Sources, slots and stage are
 // each addressed through one descriptor, every rank at a scalar offset (the
 // host checks that they fit 31 bits): pointers per rank overflow the scalar
-// registers.
+// registers. (Only the late ranks' stage stores choose a descriptor each: two
+// descriptors and a lane offset per rank, as in catch_up, were 5 % slower
+// here.)
 template <int N, bool INJECT, int C>
 __device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base, const Chunk &k,
                                               int lane, uint32_t (&done)[2][C]) {
@@ -1242,22 +1244,23 @@ __device__ __forceinline__ void step_producer(const ChainArgs &A, uint32_t base,
 }
 
 // Moves the late ranks' payload of a chunk from the stage into the slots, then
-// their stamps: the ranks catch up.
+// their stamps: the ranks catch up. The stage and the slots have one descriptor
+// each; a descriptor per late rank and side took 64 scalar registers at N = 8,
+// and up to 55 were spilled (now 36).
 template <int N>
 __device__ __forceinline__ void catch_up(const ReduceArgs &a, const Chunk &k, uint32_t g,
                                          uint32_t p, uint32_t late, int lane, uint32_t *stamp) {
     const uint32_t rank_bytes = static_cast<uint32_t>(a.geo.slot_elems) * 4u;
     const uint64_t at = static_cast<uint64_t>(p) * a.geo.slot_elems + chunk_first(a.geo, k);
     const uint32_t off = lane_offset(a.geo, k);
+    const __amdgpu_buffer_rsrc_t rs = buffer_rsrc(a.slots + at), rt = buffer_rsrc(a.stage + at);
     V16 x[N];
 #pragma unroll
     for (int r = 0; r < N; ++r)
-        x[r] = ld16_at(buffer_rsrc_if(a.stage + at, (late >> r) & 1u), off,
-                       static_cast<uint32_t>(r) * rank_bytes);
+        x[r] = ld16_at(rt, offset_if(off, (late >> r) & 1u), static_cast<uint32_t>(r) * rank_bytes);
 #pragma unroll
     for (int r = 0; r < N; ++r)
-        st16_at(buffer_rsrc_if(a.slots + at, (late >> r) & 1u), off,
-                static_cast<uint32_t>(r) * rank_bytes, x[r]);
+        st16_at(rs, offset_if(off, (late >> r) & 1u), static_cast<uint32_t>(r) * rank_bytes, x[r]);
     // the payload is published before the stamps, as a peer would; both are
     // read again by this wave alone
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
