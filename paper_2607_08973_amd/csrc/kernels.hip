@@ -1348,7 +1348,10 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
                 m = static_cast<uint32_t>(__ballot(lane < N && st != g));
                 last = m;
                 fail = m != 0 || attempts <= a.forced_retries;
-                if (MODE != kOrdered && !fail) o = sum_round<N, W>(v);
+                // the last load's sum, also of a chunk whose budget runs out
+                // (after the loop it would keep the payload registers alive)
+                if (MODE != kOrdered && (!fail || attempts >= a.max_attempts))
+                    o = sum_round<N, W>(v);
             }
         }
         if (MODE == kOrdered) {
