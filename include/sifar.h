@@ -133,7 +133,10 @@ typedef struct {
     float rms_eps;            /* RMSNorm epsilon (epilogue only) */
     uint32_t max_attempts;    /* retry budget per chunk (Sec. 4.2's loop is unbounded), >= 1 */
     uint32_t forced_retries;  /* treat the first k validations as failed (Sec. 6.3 forced-retry measurement) */
-    uint32_t spin_limit;      /* bound on the epilogue's cross-segment wait, in polls, >= 1 */
+    uint32_t spin_limit;      /* bound on the epilogue's cross-segment wait, in polls, >= 1 (at
+                                 least 1 << 20 in a one-launch step of a handle whose
+                                 waves_per_group hold a whole token: its launches would not
+                                 wait at all) */
     int32_t log_epochs;       /* decision-log ring length, in epochs, >= 1 */
     int32_t waves_per_group;  /* waves (64 lanes) per workgroup: 1, 2, 4, 8 or 16 */
     int32_t fuse_peers;       /* per-epoch steps: 1 = while epoch g is reduced the peers write

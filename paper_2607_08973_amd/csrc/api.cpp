@@ -595,6 +595,10 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
         chain_args(h, tokens, &ca);
         const int consumers = step_consumers(h, tokens);
         ca.r.groups_per_token = h->segs * consumers;
+        // A handle whose waves per workgroup hold a whole token never waits
+        // between workgroups as launches, whatever its spin_limit; here a
+        // token's chunks are workgroups of their own.
+        if (h->groups_per_token == 1 && ca.r.spin_limit < kStepSpins) ca.r.spin_limit = kStepSpins;
         rc = hip_status(launch_step(ca, h->cfg.validate, h->cfg.epilogue != 0, consumers, s));
         if (rc) return rc;
         step_enqueued(h, tokens, base);

@@ -16,6 +16,9 @@ constexpr int kChainGroupWaves = 4;         // waves per persistent-step workgro
 constexpr int kStepConsumers = 4;           // consumer waves of a one-launch step's chunk when split
 constexpr int kSplitChunks = 256;           // most chunks of a step that splits them
 constexpr int kExchPlanes = 4;              // epoch-indexed planes of the epilogue exchange
+// Least bound on the exchange wait of a one-launch step whose launches, one per
+// all-reduce, would not wait between workgroups (0.5 s or more of polls).
+constexpr uint32_t kStepSpins = 1u << 20;
 
 // x % d for a divisor fixed per launch, by a multiply-high instead of a
 // division sequence (Granlund and Montgomery, "Division by invariant integers

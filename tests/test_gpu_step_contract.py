@@ -48,3 +48,24 @@ def test_output_of_an_exhausted_budget_is_the_last_load(N, T, H, forced, withhel
         r.s.close()
     assert np.array_equal(outs[1][2], oracle.reduce(a.pool[2]))
     assert np.array_equal(outs[0], outs[1])
+
+
+# a token of four, of 16, and of one chunk (four consumer waves)
+@pytest.mark.parametrize("H,T,G", [(2048, 32, 4), (8192, 8, 16), (512, 3, 1)])
+def test_whole_token_workgroups_need_no_spin_limit(H, T, G):
+    """With waves per workgroup that hold a whole token, the epilogue's launches
+    add a token's sum of squares without a wait between workgroups, so any
+    spin_limit does; so it must in a one-launch step."""
+    N, L, steps = 8, 8, 25
+    w = synth.Workload(96, f"spin-{H}", N, (T,), H, L, 1, "act", epilogue=True)
+    runs = [StepRun(w, T, waves_per_group=G, spin_limit=1, fuse_peers=f,
+                    pool=synth.payload_pool(96, N, T, H, 5, "act")) for f in (1, 0)]
+    for step in range(steps):
+        if step % 5 == 0:
+            print(f"whole-token workgroups H={H} T={T} G={G} step {step}", flush=True)
+        for r in runs:
+            r.step(T)
+            r.s.check()
+        assert np.array_equal(to_host(runs[0].res_d), to_host(runs[1].res_d)), step
+    for r in runs:
+        r.s.close()
