@@ -424,7 +424,9 @@ int sifar_litmus(int32_t protocol, int32_t placement, int32_t pairs, int32_t tri
  * to out[tokens][hidden]. One kernel launch on `stream`, a workgroup barrier
  * between each chunk's peers and its reduction; nothing is
  * allocated or freed (no hipMalloc, hipFree or other allocating call), and
- * nothing synchronises.
+ * nothing synchronises. `out` may be one rank's partial (in place), or overlap
+ * the partials in any other way: the call is then two launches, the peers'
+ * reads and the reduction's writes.
  *
  * Scratch: the library's state for this call (slots, stamps, consumed and
  * produced words, decision log, epoch and error words) lives in one static

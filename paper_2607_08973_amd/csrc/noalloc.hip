@@ -4,7 +4,8 @@
 // decision log, the epoch base and the error word -- in one static device
 // array, for callers that cannot allocate device memory. One launch runs the
 // peers and the reduction of each chunk in a workgroup of its own, with a
-// barrier between them.
+// barrier between them; an output that overlaps the sources takes a launch for
+// each, so that every source is read before any output is written.
 //
 // The array's name is a host-side stand-in in host code, not a device
 // address: each GPU holds its own copy at its own address, which
@@ -16,6 +17,7 @@
 
 #include "sifar.h"
 #include "sifar_kernels.h"
+#include "spans.h"
 
 namespace sifar {
 namespace {
@@ -91,17 +93,63 @@ extern "C" int sifar_allreduce_noalloc(const void *src, int64_t src_rank_stride,
     geo.segs = (hidden + kChunk - 1) / kChunk;
     geo.w_max = kWMax;
     geo.slot_elems = kSlotElems;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    uint16_t *slots = reinterpret_cast<uint16_t *>(base + kOffSlots);
+    uint32_t *stamps = reinterpret_cast<uint32_t *>(base + kOffStamps);
+    uint32_t *consumed = reinterpret_cast<uint32_t *>(base + kOffConsumed);
+    uint32_t *produced = reinterpret_cast<uint32_t *>(base + kOffProduced);
+    uint32_t *log = reinterpret_cast<uint32_t *>(base + kOffLog);
+
+    const uint64_t bytes = static_cast<uint64_t>(tokens) * hidden * 2;
+    Blocks blocks{};
+    blocks.at = reinterpret_cast<uintptr_t>(src);
+    blocks.ranks = static_cast<uint64_t>(nranks);
+    blocks.rank_bytes = static_cast<uint64_t>(src_rank_stride) * 2;
+    blocks.block = bytes;
+    if (chunks_race(blocks, Span{reinterpret_cast<uintptr_t>(out), bytes})) {
+        // the epoch is passed whole: base = the always-zero word
+        const EpochRef ep{&state->zero, g, g & 1u};
+        ProduceArgs pa{};
+        pa.geo = geo;
+        pa.ep = ep;
+        pa.slots = slots;
+        pa.stamps = stamps;
+        pa.consumed = consumed;
+        pa.produced = produced;
+        pa.src = static_cast<const uint16_t *>(src);
+        pa.rank_stride = src_rank_stride;
+        pa.entries = 1;
+        pa.entries_div = make_div(1);
+        pa.inject_div = make_div(1);
+        pa.err = state->err;
+        ReduceArgs ra{};
+        ra.geo = geo;
+        ra.ep = ep;
+        ra.slots = slots;
+        ra.stamps = stamps;
+        ra.consumed = consumed;
+        ra.log = log;
+        ra.log_epochs = 1;
+        ra.log_div = make_div(1);
+        ra.inject_div = make_div(1);
+        ra.max_attempts = kAttempts;
+        ra.spin_limit = 1;
+        ra.out = static_cast<uint16_t *>(out);
+        ra.groups_per_token = 1;
+        ra.err = state->err;
+        if (launch_produce(pa, 1, s) != hipSuccess) return SIFAR_EHIP;
+        if (launch_reduce(ra, nullptr, kSpec, false, 1, s) != hipSuccess) return SIFAR_EHIP;
+        return SIFAR_OK;
+    }
     OnceArgs a{};
-    a.consumed = reinterpret_cast<uint32_t *>(base + kOffConsumed);
-    a.produced = reinterpret_cast<uint32_t *>(base + kOffProduced);
-    a.log = reinterpret_cast<uint32_t *>(base + kOffLog);
+    a.consumed = consumed;
+    a.produced = produced;
+    a.log = log;
     a.out = static_cast<uint16_t *>(out);
     a.max_attempts = kAttempts;
     a.err = state->err;
-    if (launch_once(geo, g, static_cast<const uint16_t *>(src), src_rank_stride,
-                    reinterpret_cast<uint16_t *>(base + kOffSlots),
-                    reinterpret_cast<uint32_t *>(base + kOffStamps), a,
-                    static_cast<hipStream_t>(stream)) != hipSuccess)
+    if (launch_once(geo, g, static_cast<const uint16_t *>(src), src_rank_stride, slots, stamps, a,
+                    s) != hipSuccess)
         return SIFAR_EHIP;
     return SIFAR_OK;
 }

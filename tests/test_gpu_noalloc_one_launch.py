@@ -56,3 +56,21 @@ def test_noalloc_captured_call_replays():
         torch.cuda.synchronize()
         assert np.array_equal(to_host(out), oracle.reduce(x[i])), i
         assert np.array_equal(to_host(other), oracle.reduce(x[5 - i])), i
+
+
+# in place over one rank's partial; the output some rows, one vector or one
+# whole chunk before or after the sources; and across two ranks' partials
+@pytest.mark.parametrize("N,T,H", [(8, 64, 4096), (3, 7, 1000), (2, 4, 65536)])
+@pytest.mark.parametrize("where", ["rank0", "last", "vector", "chunk", "before", "rows", "across"])
+def test_noalloc_output_over_the_sources(N, T, H, where):
+    K = T * H
+    at = {"rank0": 0, "last": (N - 1) * K, "vector": 8, "chunk": 512, "before": -8, "rows": H,
+          "across": K // 2 // 8 * 8}[where]
+    x = synth.bf16(synth.rng(97, N, T, H), (2, N, T, H), "act")
+    for rep in range(2):
+        print(f"noalloc N={N} T={T} H={H} out at {where} rep {rep}", flush=True)
+        buf = torch.zeros(8 + N * K + K, dtype=torch.int16, device=DEV)
+        buf[8:8 + N * K] = to_dev(x[rep]).reshape(-1)
+        out = buf[8 + at:8 + at + K]
+        S.sifar_allreduce_noalloc(buf[8:], K, N, T, H, out)
+        assert np.array_equal(to_host(out).reshape(T, H), oracle.reduce(x[rep]))
