@@ -216,7 +216,12 @@ int sifar_reduce_rmsnorm(sifar_t h, void *residual, const void *weight, void *y,
  *   weight, y_ring  epilogue: residual [max_tokens][hidden] (updated in place,
  *                 chained across the L reduces), weight [hidden], y_ring
  *                 [L][max_tokens][hidden]; node i writes y_ring[i].
- * Unused pointers must be NULL. Strides are in elements, multiples of 8. */
+ * Unused pointers must be NULL. Strides are in elements, multiples of 8.
+ * Overlaps: in a persistent step nothing may overlap what the step writes
+ * (out_ring, residual, y_ring). A per-epoch step takes such buffers, as
+ * launches (sifar_step): all-reduce i's writes are then done before i + 1's
+ * reduction starts, and before the peers read epoch g_(i+2)'s partials (with
+ * fuse_peers = 0, g_(i+1)'s). */
 typedef struct {
     const void *src_pool;
     int32_t pool_entries;
@@ -233,8 +238,8 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
 /* Enqueue one decode step for `tokens` tokens: L all-reduces plus one
  * epoch-counter advance. A per-epoch step with fuse_peers runs in phases:
  * produce(g1), then L-1 phases that each reduce g_i while the peers write
- * g_(i+1), then reduce(g_L). One whose chunks all fit the GPU at once as
- * two-wave workgroups (4096 chunks on MI355X; with the epilogue, a quarter of
+ * g_(i+1), then reduce(g_L). One whose buffers are apart and whose chunks all
+ * fit the GPU at once as two-wave workgroups (4096 chunks on MI355X; with the epilogue, a quarter of
  * what fits, at least 640 chunks of at most 64 per token) is one kernel launch: a
  * workgroup is one chunk, its last wave the peers, the one (or, up to 256
  * chunks, four) before it the reduction, and a workgroup barrier separates the

@@ -9,6 +9,7 @@
 #include <new>
 
 #include "sifar_kernels.h"
+#include "spans.h"
 
 using namespace sifar;
 
@@ -45,6 +46,7 @@ struct sifar_ctx {
     bool poisoned = false;
 
     bool bound = false;
+    bool overlapping = false;      // the bound buffers overlap (step_overlaps)
     sifar_step_buffers buf{};
     std::map<int32_t, hipGraphExec_t> graphs;
     hipStream_t capture = nullptr;
@@ -283,6 +285,26 @@ int capture_step(sifar_t h, int32_t tokens, hipGraphExec_t *out) {
         rc = SIFAR_EHIP;
     if (graph) (void)hipGraphDestroy(graph);
     return rc;
+}
+
+// Do the bound buffers overlap in a way that a one-launch step cannot order?
+bool buffers_overlap(const sifar_ctx *h, const sifar_step_buffers &b) {
+    const uint64_t row = static_cast<uint64_t>(h->cfg.max_tokens) * h->cfg.hidden * 2;
+    const auto at = [](const void *p) { return static_cast<uint64_t>(reinterpret_cast<uintptr_t>(p)); };
+    StepSpans s;
+    s.src.at = at(b.src_pool);
+    s.src.entries = static_cast<uint64_t>(b.pool_entries);
+    s.src.entry_bytes = static_cast<uint64_t>(b.pool_entry_stride) * 2;
+    s.src.ranks = static_cast<uint64_t>(h->cfg.nranks);
+    s.src.rank_bytes = static_cast<uint64_t>(b.pool_rank_stride) * 2;
+    s.src.block = row;
+    s.ring = {at(h->cfg.epilogue ? b.y_ring : b.out_ring),
+              row * static_cast<uint64_t>(h->cfg.reduces_per_step)};
+    if (h->cfg.epilogue) {
+        s.residual = {at(b.residual), row};
+        s.weight = {at(b.weight), static_cast<uint64_t>(h->cfg.hidden) * 2};
+    }
+    return step_overlaps(s);
 }
 
 // Epoch accounting of a step enqueued from `base`.
@@ -554,6 +576,7 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b) {
     }
     drop_graphs(h);
     h->buf = *b;
+    h->overlapping = buffers_overlap(h, *b);
     h->bound = true;
     return SIFAR_OK;
 }
@@ -584,8 +607,8 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
         return SIFAR_OK;
     }
     // A per-epoch step in one launch wherever its workgroups fit at once (the
-    // kernel's comment has both sides measured).
-    if (static_cast<int64_t>(tokens) * h->segs <= h->step_cap &&
+    // kernel's comment has both sides measured) and its buffers are apart.
+    if (static_cast<int64_t>(tokens) * h->segs <= h->step_cap && !h->overlapping &&
         source_offsets_fit(h->cfg.nranks, h->buf.pool_rank_stride)) {
         if (base != h->base_host) {
             rc = hip_status(launch_set_base(&h->state->epoch_base, base, s));

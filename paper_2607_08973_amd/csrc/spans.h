@@ -54,4 +54,20 @@ inline bool chunks_race(const Blocks &src, const Span &out) {
     return false;
 }
 
+// What a decode step is bound to: it reads the sources and the weight, writes the
+// ring of outputs and updates the residual.
+struct StepSpans {
+    Blocks src;
+    Span ring, residual, weight;
+};
+
+// A step in one launch: chunks run their whole step free of each other, sources
+// are read a phase ahead, and residual and weight stay in registers. Safe where
+// nothing the step writes overlaps anything else it touches; otherwise its
+// phases have to be launches.
+inline bool step_overlaps(const StepSpans &b) {
+    return overlap(b.src, b.ring) || overlap(b.src, b.residual) || overlap(b.ring, b.residual) ||
+           overlap(b.ring, b.weight) || overlap(b.residual, b.weight);
+}
+
 }  // namespace sifar

@@ -72,6 +72,32 @@ int main() {
         equal += !race && overlap(b, out);
         ++checked;
     }
+    // steps: a written array that overlaps anything else, each pair in turn
+    uint64_t steps[2] = {0, 0};
+    for (int i = 0; i < 200000; ++i) {
+        StepSpans b{};
+        b.src.block = draw(1, 8);
+        b.src.ranks = draw(1, 3);
+        b.src.rank_bytes = b.src.block + draw(0, 30);
+        b.src.entries = draw(1, 3);
+        b.src.entry_bytes = b.src.ranks * b.src.rank_bytes + draw(0, 30);
+        b.src.at = draw(0, 200);
+        b.ring = Span{draw(0, 600), draw(1, 24)};
+        if (rng() % 2) b.residual = Span{draw(0, 600), draw(1, 8)}, b.weight = Span{draw(0, 600), draw(1, 8)};
+        Map m(kBytes * 2, 0);  // bits: 1 source, 2 ring, 4 residual, 8 weight
+        for (uint64_t e = 0; e < b.src.entries; ++e)
+            for (uint64_t r = 0; r < b.src.ranks; ++r)
+                for (uint64_t k = 0; k < b.src.block; ++k)
+                    m.at(b.src.at + e * b.src.entry_bytes + r * b.src.rank_bytes + k) |= 1;
+        for (uint64_t k = 0; k < b.ring.size; ++k) m.at(b.ring.at + k) |= 2;
+        for (uint64_t k = 0; k < b.residual.size; ++k) m.at(b.residual.at + k) |= 4;
+        for (uint64_t k = 0; k < b.weight.size; ++k) m.at(b.weight.at + k) |= 8;
+        bool want = false;  // a written byte that something else holds too
+        for (int x : m) want |= (x & 6) != 0 && (x & (x - 1)) != 0;
+        if (step_overlaps(b) != want) return std::printf("FAIL step\n"), 1;
+        ++steps[want];
+    }
+    if (!steps[0] || !steps[1]) return std::printf("FAIL: a kind of step was never drawn\n"), 1;
     if (!met || !raced || !equal) return std::printf("FAIL: a kind of layout was never drawn\n"), 1;
     std::printf("ok %llu\n", (unsigned long long)checked);
     return 0;

@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2607_08973_amd as S
 import synth
-from sifar_harness import StepRun, inject_table, to_host
+from sifar_harness import DEV, StepRun, inject_table, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
 
@@ -69,3 +69,70 @@ def test_whole_token_workgroups_need_no_spin_limit(H, T, G):
         assert np.array_equal(to_host(runs[0].res_d), to_host(runs[1].res_d)), step
     for r in runs:
         r.s.close()
+
+
+def _flat_step(N, P, T, H, L, ring_at, fuse, seed=98):
+    """A step whose pool and ring lie in one flat buffer, the ring `ring_at`
+    elements from its start; returns the flat buffer's contents before the step
+    and after each of two steps."""
+    K = T * H
+    pool = synth.payload_pool(seed, N, T, H, P, "act")
+    flat = torch.zeros(max(P * N * K, ring_at + L * K), dtype=torch.int16, device=DEV)
+    flat[:P * N * K] = to_dev(pool).reshape(-1)
+    states = [to_host(flat)]
+    with S.Sifar(nranks=N, hidden=H, max_tokens=T, reduces_per_step=L, fuse_peers=fuse) as s:
+        S.sifar_bind_step(s.h, flat, P, N * K, K, out_ring=flat[ring_at:])
+        for _ in range(2):
+            s.step(T)
+            s.check()
+            states.append(to_host(flat))
+    return states
+
+
+# one rank: all-reduce i's output becomes (part of) the partial of a later
+# epoch, at the same chunks and shifted by a vector; two ranks: outputs over
+# partials that were read before
+@pytest.mark.parametrize("N,P,L,at,shift", [(1, 9, 5, 2, 0), (1, 10, 6, 2, 8), (1, 12, 6, 4, 512),
+                                            (2, 12, 6, 0, 0), (2, 12, 6, 0, 8)])
+@pytest.mark.parametrize("T,H", [(64, 4096), (3, 1000)])
+def test_outputs_over_the_source_pool(N, P, L, at, shift, T, H):
+    """The step runs one all-reduce after the other over whatever the buffers
+    hold: what an output overwrote is what a later epoch reads."""
+    K = T * H
+    ring_at = at * N * K + shift
+    print(f"outputs over the pool N={N} P={P} L={L} ring at {ring_at} T={T} H={H}", flush=True)
+    states = _flat_step(N, P, T, H, L, ring_at, 1)
+    mem = states[0].copy()
+    for step in range(2):
+        for i in range(L):
+            e = (step * (L + L % 2) + i) % P     # an odd chain skips an epoch
+            x = mem[e * N * K:(e + 1) * N * K].reshape(N, T, H)
+            mem[ring_at + i * K:ring_at + (i + 1) * K] = oracle.reduce(x).reshape(-1)
+        assert np.array_equal(states[1 + step], mem), f"step {step}"
+
+
+@pytest.mark.parametrize("alias", ["residual", "weight"])
+def test_epilogue_outputs_over_its_own_inputs(alias):
+    """y of all-reduce 1 overwrites the residual, or the weight, that the next
+    ones read: word for word what separate launches do."""
+    N, T, H, L = 4, 1, 4096, 5
+    pool = to_dev(synth.payload_pool(99, N, T, H, 7, "act"))
+    out = []
+    for fuse in (1, 0):
+        y = torch.zeros((L, T, H), dtype=torch.int16, device=DEV)
+        res, wgt = to_dev(synth.residual_init(99, T, H)), to_dev(synth.rms_weight(99, H))
+        if alias == "residual":
+            y[1].copy_(res)
+            res = y[1]
+        else:
+            y[1, 0].copy_(wgt)
+            wgt = y[1, 0]
+        with S.Sifar(nranks=N, hidden=H, max_tokens=T, reduces_per_step=L, epilogue=1,
+                     fuse_peers=fuse) as s:
+            s.bind_step(pool, residual=res, weight=wgt, y_ring=y)
+            for _ in range(2):
+                print(f"epilogue over its {alias} fuse={fuse}", flush=True)
+                s.step(T)
+                s.check()
+        out.append((to_host(y), to_host(res)))
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
