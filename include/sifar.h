@@ -258,6 +258,12 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
  * from a device-resident counter, so neither a replay nor a persistent
  * launch needs per-all-reduce host work. Requires no produced-but-unreduced
  * epoch (SIFAR_ESTATE).
+ * Steps are not for recording into a caller's stream capture (the host counts
+ * a step when it is enqueued; sifar_allreduce_noalloc is for captures). On a
+ * capturing stream a per-epoch step is always the graph of launches, which the
+ * HIP runtime does not record: it runs at once. A persistent step is recorded;
+ * each replay then advances the device's epochs while sifar_epochs has counted
+ * one step, so mix no other call with its replays.
  * A persistent step needs all its waves resident at once (checked at init
  * against an otherwise idle GPU); persistent steps of several handles that run
  * concurrently on different streams may not fit together, and then end with a

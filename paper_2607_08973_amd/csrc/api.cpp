@@ -307,6 +307,12 @@ bool buffers_overlap(const sifar_ctx *h, const sifar_step_buffers &b) {
     return step_overlaps(s);
 }
 
+// Is `s` recording a stream capture?
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
 // Epoch accounting of a step enqueued from `base`.
 void step_enqueued(sifar_t h, int32_t tokens, uint32_t base) {
     const uint32_t L = static_cast<uint32_t>(h->cfg.reduces_per_step);
@@ -607,9 +613,11 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
         return SIFAR_OK;
     }
     // A per-epoch step in one launch wherever its workgroups fit at once (the
-    // kernel's comment has both sides measured) and its buffers are apart.
+    // kernel's comment has both sides measured) and its buffers are apart. Not
+    // on a capturing stream: recorded, a step would run once per replay while
+    // the host has counted it once; a graph of launches is not recorded.
     if (static_cast<int64_t>(tokens) * h->segs <= h->step_cap && !h->overlapping &&
-        source_offsets_fit(h->cfg.nranks, h->buf.pool_rank_stride)) {
+        source_offsets_fit(h->cfg.nranks, h->buf.pool_rank_stride) && !capturing(s)) {
         if (base != h->base_host) {
             rc = hip_status(launch_set_base(&h->state->epoch_base, base, s));
             if (rc) return rc;

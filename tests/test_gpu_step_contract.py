@@ -136,3 +136,43 @@ def test_epilogue_outputs_over_its_own_inputs(alias):
                 s.check()
         out.append((to_host(y), to_host(res)))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("epilogue", [False, True])
+@pytest.mark.parametrize("fuse", [1, 0])
+def test_step_on_a_capturing_stream_is_not_recorded(fuse, epilogue):
+    """On a capturing stream a per-epoch step runs at once, whichever kernels
+    would otherwise run it, and the host's epochs stay the device's: replays of
+    the (empty) capture change nothing and the next steps go on."""
+    w = synth.Workload(100, "capture", 4, (3,), 1000, 4, 1, "act", epilogue=epilogue)
+    run = StepRun(w, 3, fuse_peers=fuse, pool=synth.payload_pool(100, 4, 3, 1000, 23, "act"))
+    res = run.res0.copy() if epilogue else None
+
+    def check(epochs, what):
+        nonlocal res
+        torch.cuda.synchronize()
+        run.s.check()
+        assert run.s.epochs() == (epochs[-1] + 1, epochs[-1] + 1), what
+        if epilogue:
+            _, r, y = oracle.reduce_chain(run.pool, epochs, 3, epilogue=(res, run.weight, w.rms_eps))
+            res = r[-1]
+            assert np.array_equal(to_host(run.res_d), res), what
+        else:
+            exp = oracle.reduce_chain(run.pool, epochs, 3)
+            assert np.array_equal(to_host(run.out_d), np.stack(exp)), what
+
+    check(run.step(3), "first")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        graph.capture_begin(capture_error_mode="relaxed")
+        try:
+            epochs = run.step(3)
+        finally:
+            graph.capture_end()
+    check(epochs, "captured")
+    for k in range(2):
+        print(f"after a capture fuse={fuse} epilogue={epilogue} step {k}", flush=True)
+        graph.replay()
+        check(run.step(3), f"after replay {k}")
+    run.s.close()
