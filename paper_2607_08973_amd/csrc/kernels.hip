@@ -1333,7 +1333,8 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
             uint32_t m = static_cast<uint32_t>(__ballot(lane < N && st != g));
             first = last = m;
             bool fail = m != 0 || a.forced_retries >= 1;
-            while (fail) {
+            // without a table no stamp is late: the loop stays out of the way
+            while (INJECT ? fail : __builtin_expect(fail, false)) {
                 if (attempts >= a.max_attempts) {
                     if (lane == 0) latch(a.err, kErrRetryBudget, g, k.c, attempts);
                     break;
