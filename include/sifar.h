@@ -272,6 +272,12 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
  * microseconds: a wait that has lasted 64 polls also reads the error word. */
 int sifar_step(sifar_t h, int32_t tokens, void *stream);
 
+/* How sifar_step runs `tokens` tokens with the buffers bound now (none: buffers
+ * that are apart): plan[0] kernel launches or graph kernel nodes of the step
+ * (1: one launch), plan[1] consumer waves per chunk, plan[2] the most chunks of
+ * a per-epoch step in one launch on this handle (0: none is). */
+int sifar_step_plan(sifar_t h, int32_t tokens, int32_t plan[3]);
+
 /* ---- injection, logs, state --------------------------------------------------- */
 
 /* Install (copies) a host table of `entries` uint16 words (late | withheld << 8)
@@ -305,6 +311,13 @@ int sifar_read_log(sifar_t h, uint32_t *host_dst, size_t words);
  * stamp is read and the words are 0. `words` must be at most
  * log_epochs * w_max * 2N. */
 int sifar_read_stamp_log(sifar_t h, uint32_t *host_dst, size_t words);
+
+/* Copy the placement words to host memory (synchronises the device): where the
+ * waves of the last persistent step ran. Word c is chunk c's consumer, word
+ * w_max + c its producer: (the step's first epoch << 32) | 0x100 | XCD, 0 before
+ * the first such step. (One-launch steps with the epilogue write the consumers'
+ * words.) `words` must be at most 2 * w_max. */
+int sifar_read_placement(sifar_t h, uint64_t *host_dst, size_t words);
 
 /* Next epoch to produce and next epoch to reduce (host-side accounting). */
 int sifar_epochs(sifar_t h, uint32_t *next_produce, uint32_t *next_reduce);

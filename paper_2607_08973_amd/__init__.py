@@ -72,8 +72,8 @@ CHUNK = 512  # elements per chunk (one 64-lane wave, 16 bytes per lane)
 EXPORTS = (
     "sifar_config_default", "sifar_version", "sifar_init", "sifar_destroy",
     "sifar_produce", "sifar_reduce", "sifar_reduce_rmsnorm", "sifar_bind_step",
-    "sifar_step", "sifar_set_injection", "sifar_log_geometry", "sifar_read_log",
-    "sifar_read_stamp_log",
+    "sifar_step", "sifar_step_plan", "sifar_set_injection", "sifar_log_geometry",
+    "sifar_read_log", "sifar_read_stamp_log", "sifar_read_placement",
     "sifar_epochs", "sifar_status", "sifar_error_info", "sifar_strerror", "sifar_floor",
     "sifar_litmus", "sifar_allreduce_noalloc",
 )
@@ -162,11 +162,13 @@ def load(path: str = LIB_PATH):
         "sifar_reduce_rmsnorm": (ctypes.c_int, [P, P, P, P, I32, P]),
         "sifar_bind_step": (ctypes.c_int, [P, ctypes.POINTER(sifar_step_buffers)]),
         "sifar_step": (ctypes.c_int, [P, I32, P]),
+        "sifar_step_plan": (ctypes.c_int, [P, I32, ctypes.POINTER(I32)]),
         "sifar_set_injection": (ctypes.c_int, [P, P, I32, I32]),
         "sifar_log_geometry": (ctypes.c_int, [P, ctypes.POINTER(I32), ctypes.POINTER(I32),
                                               ctypes.POINTER(I32)]),
         "sifar_read_log": (ctypes.c_int, [P, P, SZ]),
         "sifar_read_stamp_log": (ctypes.c_int, [P, P, SZ]),
+        "sifar_read_placement": (ctypes.c_int, [P, P, SZ]),
         "sifar_epochs": (ctypes.c_int, [P, ctypes.POINTER(U32), ctypes.POINTER(U32)]),
         "sifar_status": (ctypes.c_int, [P]),
         "sifar_error_info": (ctypes.c_int, [P, ctypes.POINTER(U32)]),
@@ -269,6 +271,13 @@ def sifar_step(h: int, tokens: int, stream=None) -> None:
     _check("sifar_step", load().sifar_step(h, tokens, _stream(stream)))
 
 
+def sifar_step_plan(h: int, tokens: int):
+    """(launches, consumer waves per chunk, most chunks of a one-launch step)."""
+    plan = (ctypes.c_int32 * 3)()
+    _check("sifar_step_plan", load().sifar_step_plan(h, tokens, plan))
+    return tuple(plan)
+
+
 def sifar_set_injection(h: int, table: Optional[Sequence[int]], mode: int) -> None:
     if mode == SIFAR_INJECT_SLOT_OVERRUN:
         _check("sifar_set_injection", load().sifar_set_injection(h, None, 0, mode))
@@ -302,6 +311,15 @@ def sifar_read_stamp_log(h: int, nranks: int):
     epochs, _, w_max = sifar_log_geometry(h)
     out = np.zeros(epochs * w_max * 2 * nranks, dtype=np.uint32)
     _check("sifar_read_stamp_log", load().sifar_read_stamp_log(h, out.ctypes.data, out.size))
+    return out
+
+
+def sifar_read_placement(h: int):
+    """Placement words of the consumers and the producers, [2][w_max]."""
+    import numpy as np
+    _, _, w_max = sifar_log_geometry(h)
+    out = np.zeros((2, w_max), dtype=np.uint64)
+    _check("sifar_read_placement", load().sifar_read_placement(h, out.ctypes.data, out.size))
     return out
 
 
@@ -405,6 +423,9 @@ class Sifar:
     def step(self, tokens, stream=None):
         sifar_step(self.h, tokens, stream)
 
+    def step_plan(self, tokens):
+        return sifar_step_plan(self.h, tokens)
+
     def set_injection(self, table, mode=SIFAR_INJECT_DETERMINISTIC):
         sifar_set_injection(self.h, table, mode)
 
@@ -413,6 +434,9 @@ class Sifar:
 
     def read_stamp_log(self):
         return sifar_read_stamp_log(self.h, self.cfg.nranks)
+
+    def read_placement(self):
+        return sifar_read_placement(self.h)
 
     def log_geometry(self):
         return sifar_log_geometry(self.h)

@@ -13,6 +13,13 @@
 
 using namespace sifar;
 
+// 0 builds a library whose per-epoch steps are all graphs of launches, for the
+// tests of that path at sizes that one launch serves. (A macro, as the plane
+// alignment is.)
+#ifndef SIFAR_ONE_LAUNCH
+#define SIFAR_ONE_LAUNCH 1
+#endif
+
 struct sifar_ctx {
     sifar_config cfg{};
     int device = 0;
@@ -190,6 +197,14 @@ int chain_waves(const sifar_ctx *h, int32_t tokens) {
                    chunks >= 512
                ? kChainGroupWaves
                : 1;
+}
+
+// Does a per-epoch step of `tokens` tokens run in one launch? Wherever its
+// workgroups fit at once (the kernel's comment has both sides measured) and its
+// buffers are apart.
+bool one_launch(const sifar_ctx *h, int32_t tokens) {
+    return static_cast<int64_t>(tokens) * h->segs <= h->step_cap && !h->overlapping &&
+           source_offsets_fit(h->cfg.nranks, h->buf.pool_rank_stride);
 }
 
 // Consumer waves per chunk of a one-launch per-epoch step (the kernel's comment
@@ -421,8 +436,8 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
         h->chain_grouping = c.nranks * kChainGroupWaves <= kLanes && gcap > 0 &&
                             waves / kChainGroupWaves <= gcap;
     }
-    if (!c.persistent && c.fuse_peers && c.buffers == 2 && (!c.epilogue || h->segs <= kLanes) &&
-        step_offsets_fit(c.nranks, h->slot_elems)) {
+    if (SIFAR_ONE_LAUNCH && !c.persistent && c.fuse_peers && c.buffers == 2 &&
+        (!c.epilogue || h->segs <= kLanes) && step_offsets_fit(c.nranks, h->slot_elems)) {
         h->step_cap = max_active_step_groups(c.nranks, c.validate, c.epilogue != 0);
         // With the epilogue a token's workgroups wait for each other. A
         // quarter of the GPU's places leaves room for the steps of three more
@@ -612,12 +627,10 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
         step_enqueued(h, tokens, base);
         return SIFAR_OK;
     }
-    // A per-epoch step in one launch wherever its workgroups fit at once (the
-    // kernel's comment has both sides measured) and its buffers are apart. Not
-    // on a capturing stream: recorded, a step would run once per replay while
-    // the host has counted it once; a graph of launches is not recorded.
-    if (static_cast<int64_t>(tokens) * h->segs <= h->step_cap && !h->overlapping &&
-        source_offsets_fit(h->cfg.nranks, h->buf.pool_rank_stride) && !capturing(s)) {
+    // Not in one launch on a capturing stream: recorded, a step would run once
+    // per replay while the host has counted it once; a graph of launches is not
+    // recorded.
+    if (one_launch(h, tokens) && !capturing(s)) {
         if (base != h->base_host) {
             rc = hip_status(launch_set_base(&h->state->epoch_base, base, s));
             if (rc) return rc;
@@ -651,6 +664,17 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
     }
     if (hipGraphLaunch(exec, s) != hipSuccess) return SIFAR_EHIP;
     step_enqueued(h, tokens, base);
+    return SIFAR_OK;
+}
+
+int sifar_step_plan(sifar_t h, int32_t tokens, int32_t plan[3]) {
+    if (!h || !plan || tokens < 1 || tokens > h->cfg.max_tokens) return SIFAR_EINVAL;
+    const int L = h->cfg.reduces_per_step;
+    const bool fused = h->cfg.fuse_peers && h->cfg.buffers == 2;
+    const bool one = h->cfg.persistent || one_launch(h, tokens);
+    plan[0] = one ? 1 : fused ? L + 2 : 2 * L + 1;
+    plan[1] = one && !h->cfg.persistent ? step_consumers(h, tokens) : 1;
+    plan[2] = h->step_cap;
     return SIFAR_OK;
 }
 
@@ -717,6 +741,15 @@ int sifar_read_stamp_log(sifar_t h, uint32_t *host_dst, size_t words) {
     if (hipDeviceSynchronize() != hipSuccess) return SIFAR_EHIP;
     if (hipMemcpy(host_dst, h->stamp_log, words * sizeof(uint32_t), hipMemcpyDeviceToHost) !=
         hipSuccess)
+        return SIFAR_EHIP;
+    return SIFAR_OK;
+}
+
+int sifar_read_placement(sifar_t h, uint64_t *host_dst, size_t words) {
+    if (!h || !host_dst) return SIFAR_EINVAL;
+    if (words > static_cast<size_t>(2) * h->w_max) return SIFAR_EINVAL;
+    if (hipDeviceSynchronize() != hipSuccess) return SIFAR_EHIP;
+    if (hipMemcpy(host_dst, h->place, words * sizeof(uint64_t), hipMemcpyDeviceToHost) != hipSuccess)
         return SIFAR_EHIP;
     return SIFAR_OK;
 }

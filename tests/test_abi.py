@@ -89,6 +89,9 @@ def test_null_handle_rejected():
     assert L.sifar_reduce(None, None, 1, None) == S.SIFAR_EINVAL
     assert L.sifar_step(None, 1, None) == S.SIFAR_EINVAL
     assert L.sifar_status(None) == S.SIFAR_EINVAL
+    plan = (ctypes.c_int32 * 3)()
+    assert L.sifar_step_plan(None, 1, plan) == S.SIFAR_EINVAL
+    assert L.sifar_read_placement(None, ctypes.byref(plan), 1) == S.SIFAR_EINVAL
     assert L.sifar_init(None, None) == S.SIFAR_EINVAL
     L.sifar_destroy(None)
 

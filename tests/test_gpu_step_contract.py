@@ -82,6 +82,7 @@ def _flat_step(N, P, T, H, L, ring_at, fuse, seed=98):
     states = [to_host(flat)]
     with S.Sifar(nranks=N, hidden=H, max_tokens=T, reduces_per_step=L, fuse_peers=fuse) as s:
         S.sifar_bind_step(s.h, flat, P, N * K, K, out_ring=flat[ring_at:])
+        assert s.step_plan(T)[0] == L + 2   # not in one launch
         for _ in range(2):
             s.step(T)
             s.check()

@@ -10,6 +10,7 @@ import pytest
 import torch
 
 import oracle
+import paper_2607_08973_amd as S
 import synth
 from sifar_harness import StepRun, inject_table, to_host, ulp_distance
 
@@ -92,6 +93,8 @@ def test_batches_on_both_sides_of_the_launch_rule():
     r = StepRun(w, T_max, pool=pool)
     for tokens in (256, 257, 1, 258, 255):
         print(f"launch rule T={tokens}", flush=True)
+        assert r.s.step_plan(tokens) == ((1, 1, 4096) if tokens <= 256 else (L + 2, 1, 4096)) or \
+            tokens == 1 and r.s.step_plan(1) == (1, 4, 4096)
         epochs = r.step(tokens)
         got = to_host(r.out_d)
         exp = oracle.reduce_chain(pool, epochs, tokens)
@@ -164,8 +167,12 @@ def test_epilogue_batches_on_both_sides_of_the_launch_rule():
     pool = synth.payload_pool(88, N, T_max, H, 5, "act")
     r = StepRun(w, T_max, pool=pool)
     res = r.res0.copy()
+    crossed = set()
     for tokens in (40, 66, 1, 64, 65, 33):
         print(f"epilogue launch rule T={tokens}", flush=True)
+        launches, _, cap = r.s.step_plan(tokens)
+        assert 640 <= cap <= 1024 and launches == (1 if tokens * 16 <= cap else L + 2)
+        crossed.add(launches)
         epochs = r.step(tokens)
         _, r_list, y_list = oracle.reduce_chain(pool, epochs, tokens,
                                                 epilogue=(res[:tokens], r.weight, w.rms_eps))
@@ -174,8 +181,37 @@ def test_epilogue_batches_on_both_sides_of_the_launch_rule():
         y = to_host(r.y_d)
         for i in range(L):
             assert ulp_distance(y[i, :tokens], y_list[i]).max() <= 1, (tokens, i)
+    assert crossed == {1, L + 2}
     r.s.check()
     r.s.close()
+
+
+@pytest.mark.parametrize("N", range(1, 9))
+@pytest.mark.parametrize("mode", ["spec", "ordered", "none"])
+def test_small_steps_are_one_launch(N, mode):
+    """The rule itself, from the plan the handle states: 16 two-wave workgroups
+    on each of 256 CUs (with the epilogue a quarter of what fits, 640 chunks at
+    least), four consumer waves up to 256 chunks; everything else is launches."""
+    def plan(tokens, hidden=4096, L=6, table=False, **cfg):
+        with S.Sifar(nranks=N, hidden=hidden, max_tokens=tokens, reduces_per_step=L, validate=mode,
+                     **cfg) as s:
+            if table:
+                s.set_injection([0] * L)
+            return s.step_plan(tokens)
+
+    assert plan(1) == (1, 4, 4096) and plan(32) == (1, 4, 4096)
+    assert plan(33) == (1, 1, 4096) and plan(512) == (1, 1, 4096)
+    assert plan(513) == (8, 1, 4096)
+    launches, waves, cap = plan(8, 8192, epilogue=1)
+    assert (launches, waves) == (1, 4) and 640 <= cap <= 1024
+    assert plan(cap // 16, 8192, epilogue=1) == (1, 1, cap)
+    assert plan(cap // 16 + 1, 8192, epilogue=1) == (8, 1, cap)
+    assert plan(2, 65 * 512, epilogue=1, waves_per_group=2) == (8, 1, 0)  # 65 chunks a token
+    assert plan(4, fuse_peers=0) == (13, 1, 0) and plan(4, buffers=1) == (13, 1, 0)
+    if mode == "ordered":
+        assert plan(4, persistent=1) == (1, 1, 0)
+    if mode != "none":
+        assert plan(1, table=True) == (1, 1, 4096)
 
 
 def test_epilogue_steps_of_four_handles_at_once():
