@@ -78,6 +78,17 @@ class StepRun:
         return list(range(g1 - self.L, g1))
 
 
+def pairs_across(run: StepRun, tokens: int) -> float:
+    """Share of the last persistent step's chunks whose consumer and producer
+    ran on different XCDs, from the placement words the waves wrote."""
+    chunks = tokens * run.s.log_geometry()[1]
+    words = run.s.read_placement()[:, :chunks]
+    first = run.s.epochs()[0] - run.L
+    assert np.all(words >> 32 == first) and np.all(words & 0x100), "words of another step"
+    xcd = words & 0xFF
+    return float(np.mean(xcd[0] != xcd[1]))
+
+
 def read_stamp_log(s: "S.Sifar") -> np.ndarray:
     """The raw-stamp log as [log_epochs][w_max][2][N]: rank r's stamp at a
     chunk's first (index 0) and last (index 1) validation."""

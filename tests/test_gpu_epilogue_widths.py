@@ -1,8 +1,9 @@
 """Residual-add + RMSNorm at every kind of exchange width: one chunk per token
 (no exchange), two, an odd number, one lane row of 16, one more, 33 and 64 (the
 most), with rows that end inside a lane group and one of 8 elements; persistent
-steps, per-epoch steps in one launch, and as launches of several workgroup widths, four chained nodes, two steps. Residual
-bit-exact, y within 1 bf16 step of the float64 oracle."""
+steps, per-epoch steps in one launch, and as launches of several workgroup
+widths, four chained nodes, two steps. Residual bit-exact, y within 1 bf16 step
+of the float64 oracle."""
 from __future__ import annotations
 
 import numpy as np

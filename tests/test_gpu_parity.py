@@ -18,8 +18,8 @@ from oracle import ref_np, sim
 
 pytestmark = pytest.mark.gpu
 
-from sifar_harness import (DEV, StepRun, expected_log_words, inject_table, read_stamp_log,
-                           replay_logs, to_dev, to_host, ulp_distance)
+from sifar_harness import (DEV, StepRun, expected_log_words, inject_table, pairs_across,
+                           read_stamp_log, replay_logs, to_dev, to_host, ulp_distance)
 
 ORDERS = {"spec": "spec", "ordered": "ordered"}
 
@@ -106,8 +106,8 @@ def test_graph_llama_decode_steps(mode, fuse):
 
 
 def test_graph_llama_full_run_sampled():
-    """The benchmark's configuration: 100 decode steps per batch size, every
-    step replayed from the captured graph; outputs sampled every 9th step."""
+    """The benchmark's shapes as per-epoch steps: 100 decode steps per batch
+    size, one launch each; outputs sampled every 9th step."""
     w = synth.LLAMA8B_DECODE
     run = StepRun(w, 8)
     for T in w.tokens:
@@ -157,7 +157,7 @@ def test_stale_injection_deterministic(order, forced, fuse):
 def test_spec_stress_full_length():
     """The speculation stress workload at its stated length: N = 8, 4 tokens,
     64 all-reduces per step, 200 steps, each rank's stamp late with p = 0.1.
-    Per-epoch launches with the peers fused into the reduction's launch, the
+    Per-epoch steps with the peers one epoch ahead (one launch each), the
     paper's speculative reduction. A late rank's payload waits in the stage
     and its slot still holds its previous epoch when the reduction first loads
     it, so only a retry that reloads the payload gets the sum right. Every
@@ -293,7 +293,7 @@ def test_protocol_order_errors():
 
 
 def test_eager_then_graph_epochs_continue():
-    """Eager epochs, then graph steps: epochs stay unique, parities stay right."""
+    """Eager epochs, then per-epoch steps: epochs stay unique, parities stay right."""
     w = synth.Workload(60, "mix", 4, (2,), 2048, 6, 1, "normal")
     run = StepRun(w, 2)
     extra = to_dev(synth.payload_pool(61, 4, 2, 2048, 3, "normal"))
@@ -348,7 +348,7 @@ SWEEP_POINTS = [(w.nranks, w.tokens[0], w.hidden) for w in synth.PAYLOAD_SWEEP]
 @pytest.mark.parametrize("N,T,H", SWEEP_POINTS)
 def test_payload_sweep_points(N, T, H, persistent):
     """Every point of the latency-to-bandwidth sweep (8 KiB to 4 MiB per rank),
-    U(-1, 1) values, full outputs of a 4-reduce step, per-launch and
+    U(-1, 1) values, full outputs of a 4-reduce step, per-epoch and
     persistent (where the persistent step fits the GPU)."""
     w = synth.Workload(4, f"sweep-n{N}-t{T}-h{H}", N, (T,), H, 4, 1, "uniform")
     print(f"sweep N={N} T={T} H={H} persistent={persistent}", flush=True)
@@ -731,11 +731,10 @@ def test_persistent_late_stamps_log_replay(T):
 def test_persistent_ragged_shapes(N, T, H):
     """Persistent steps on shapes off the benchmark grid: 3896 leaves a partial
     last chunk in each row (8 chunks per token, 128 chunks); 4608 has 9 chunks
-    per token; N = 3 with 64 chunks. The next four have a number of workgroups
-    per plane that is not a multiple of the 8 XCDs (2, 9, 1 and 45 chunks), so
-    a chunk's producer and consumer run on different XCDs and meet only through
-    agent-scope memory. Then one rank, an odd rank count, and 1024 chunks at
-    N = 6."""
+    per token; N = 3 with 64 chunks. The next four have a number of chunks that
+    is not a multiple of the 8 XCDs (2, 9, 1 and 45), so the grid holds idle
+    rows that keep a chunk's producer and consumer on one XCD. Then one rank,
+    an odd rank count, and 1024 chunks at N = 6."""
     w = synth.Workload(73, f"ragged-{N}-{T}-{H}", N, (T,), H, 12, 1, "normal")
     run = StepRun(w, T, persistent=1)
     for rep in range(3):
@@ -749,20 +748,22 @@ def test_persistent_ragged_shapes(N, T, H):
     run.s.close()
 
 
-def test_persistent_cross_xcd_many_steps():
-    """64-all-reduce persistent steps, 2 chunks per plane (producer and
-    consumer of a chunk on different XCDs), 40 steps, sampled."""
+def test_persistent_cross_xcd_many_steps(grid):
+    """64-all-reduce persistent steps, 2 chunks per plane, 40 steps, sampled:
+    with the library's grid (producer and consumer of a chunk on one XCD) and
+    without its idle rows (on different XCDs)."""
     w = synth.Workload(74, "cross-xcd", 8, (1,), 1024, 64, 40, "act")
     run = StepRun(w, 1, persistent=1)
     for step in range(w.steps):
         epochs = run.step(1)
         if step % 7 == 0:
-            print(f"cross-xcd step {step}", flush=True)
+            print(f"{grid} step {step}", flush=True)
             got = to_host(run.out_d)
             for i in range(0, w.reduces_per_step, 3):
                 g = epochs[i]
                 exp = oracle.reduce(run.pool[(g - 1) % run.pool.shape[0]][:, :1])
                 assert np.array_equal(got[i, :1], exp), f"step={step} node={i}"
+            assert pairs_across(run, 1) == (grid == "unpadded")
     run.s.check()
     log = run.s.read_log()[:, :2]
     assert np.all((log >> 24) == 0)
@@ -770,31 +771,34 @@ def test_persistent_cross_xcd_many_steps():
 
 
 @pytest.mark.parametrize("N,T,H", [(8, 5, 4608), (8, 1, 1024)])
-def test_persistent_cross_xcd_every_output(N, T, H):
-    """150 persistent steps of 12 all-reduces with each chunk's producer and
-    consumer on different XCDs, every output checked. A reduction that loaded
+def test_persistent_cross_xcd_every_output(grid, N, T, H):
+    """150 persistent steps of 12 all-reduces, every output checked, each
+    chunk's producer and consumer on one XCD (the library's grid) or on
+    different ones (without its idle rows). Across XCDs a reduction that loaded
     the payload together with the stamps (the paper's speculation) accepted a
     rank's previous epoch under a fresh stamp in ~2 % of these all-reduces;
     the persistent step must validate before it loads."""
     w = synth.Workload(75, f"cross-xcd-{N}-{T}-{H}", N, (T,), H, 12, 150, "normal")
     run = StepRun(w, T, persistent=1)
     P = run.pool.shape[0]
-    bad = []
+    bad, across = [], set()
     for step in range(w.steps):
         if step % 50 == 0:
-            print(f"cross-xcd every output N={N} T={T} H={H} step {step}", flush=True)
+            print(f"{grid} every output N={N} T={T} H={H} step {step}", flush=True)
         epochs = run.step(T)
         got = to_host(run.out_d)
+        across.add(pairs_across(run, T))
         for i, g in enumerate(epochs):
             if not np.array_equal(got[i, :T], oracle.reduce(run.pool[(g - 1) % P][:, :T])):
                 bad.append((step, i))
     run.s.check()
     run.s.close()
     assert not bad, f"{len(bad)} of {w.steps * w.reduces_per_step} all-reduces differ: {bad[:5]}"
+    assert across == {float(grid == "unpadded")}
 
 
 def test_persistent_after_eager_and_graph_steps():
-    """Eager epochs, fused graph steps and persistent steps on one handle."""
+    """Eager epochs and persistent steps on one handle."""
     w = synth.Workload(71, "mixed-modes", 8, (2,), 4096, 6, 1, "act")
     pool = synth.payload_pool(71, 8, 2, 4096, 19, "act")
     run_p = StepRun(w, 2, persistent=1, pool=pool)
@@ -896,11 +900,12 @@ def test_two_persistent_handles_step_concurrently():
 @pytest.mark.parametrize("G", [2, 8, 16])
 @pytest.mark.parametrize("mode", ["spec", "ordered"])
 def test_graph_steps_multiwave_groups(G, mode):
-    """Per-launch steps with several waves per workgroup: the shape word the
-    kernel receives as a preloaded argument carries log2 of the waves per
-    group, and rows of 9 and 3 chunks leave idle waves in the last group of
-    each token (they must load in bounds and store nothing). Every output of
-    two steps per batch size."""
+    """Waves per workgroup of a per-epoch step's handle. They do not concern a
+    step in one launch. As launches (the fallback library's tests call this
+    too) the shape word the kernel receives as a preloaded argument carries
+    log2 of the waves per group, and rows of 9 and 3 chunks leave idle waves in
+    the last group of each token (they must load in bounds and store nothing).
+    Every output of two steps per batch size."""
     w = synth.Workload(82, f"multiwave-g{G}", 8, (1, 5), 4608, 8, 1, "act")
     run = StepRun(w, 5, validate=mode, waves_per_group=G, pool=synth.payload_pool(82, 8, 5, 4608, 7, "act"))
     for T in (1, 5):
@@ -941,7 +946,7 @@ def _random_shapes(n=12, seed=2607):
 
 @pytest.mark.parametrize("case", range(12))
 def test_random_shapes_both_step_forms(case):
-    """The same seeded shape as a captured per-launch step (SPEC) and as a
+    """The same seeded shape as a per-epoch step (SPEC) and as a
     persistent step (ORDERED), two steps each: every all-reduce output
     bit-exact, or with the epilogue the residual bit-exact and every y within
     1 bf16 step."""
