@@ -174,10 +174,6 @@ __device__ __forceinline__ void st_flag(uint32_t *p, uint32_t v, bool local) {
         __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void st_release(uint32_t *p, uint32_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Makes every load that fed `v` complete before any later instruction issues:
 // the value is consumed by an (empty) compiler barrier, so the compiler must
 // wait for it there.

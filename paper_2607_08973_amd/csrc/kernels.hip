@@ -150,10 +150,11 @@ __device__ __forceinline__ void load_sources(const ProduceArgs &a, const Chunk &
     for (int r = 0; r < N; ++r) v[r] = ld16_buffer<0>(src + r * a.rank_stride, off);
 }
 
-// The same through one descriptor, every rank's slot at a scalar offset from
-// rank 0's (launch_chain checks that the offsets fit): one scalar instruction
-// per store instead of three for a descriptor of its own, so the stores the
-// publication waits for leave back to back.
+// The sources in registers, written into the slots of parity p through one
+// descriptor, every rank's slot at a scalar offset from rank 0's (launch_chain
+// checks that the offsets fit): one scalar instruction per store instead of
+// three for a descriptor of its own, so the stores the publication waits for
+// leave back to back.
 template <int N>
 __device__ __forceinline__ void store_slots_at(const ProduceArgs &a, const Chunk &k, uint32_t p,
                                                const V16 (&v)[N]) {
@@ -165,19 +166,6 @@ __device__ __forceinline__ void store_slots_at(const ProduceArgs &a, const Chunk
     if (k.lane_ok) {
 #pragma unroll
         for (int r = 0; r < N; ++r) st16_at(rs, off, static_cast<uint32_t>(r) * rank_bytes, v[r]);
-    }
-}
-
-// ... written into the slots of parity p.
-template <int N>
-__device__ __forceinline__ void store_slots(const ProduceArgs &a, const Chunk &k, uint32_t p,
-                                            const V16 (&v)[N]) {
-    const Geometry &geo = a.geo;
-    uint16_t *dst = a.slots + static_cast<uint64_t>(p) * geo.slot_elems + chunk_first(geo, k);
-    const uint32_t off = lane_offset(geo, k);
-    if (k.lane_ok) {
-#pragma unroll
-        for (int r = 0; r < N; ++r) st16_buffer(dst + r * 2 * geo.slot_elems, off, v[r]);
     }
 }
 
@@ -513,7 +501,7 @@ __device__ __forceinline__ float lanes_sum(float v, int n, int lane) {
 __device__ __forceinline__ void residual_rmsnorm(const ReduceArgs &a, const Chunk &k, uint32_t g,
                                                  const V16 &o, const V16 &rv,
                                                  const V16 &wv, uint16_t *y, int lane, int wave,
-                                                 int G, int q, bool xlocal = false) {
+                                                 int G, int q) {
     const Geometry &geo = a.geo;
     // res' = bf16(a + res), with a = the bf16 all-reduce result.
     V16 nr;
@@ -548,11 +536,7 @@ __device__ __forceinline__ void residual_rmsnorm(const ReduceArgs &a, const Chun
                            static_cast<size_t>(k.t) * Q;
             if (lane == 0) {
                 const uint64_t word = (static_cast<uint64_t>(g) << 32) | __float_as_uint(grp);
-                // all groups of the token on this XCD: the word meets them in its L2
-                if (xlocal)
-                    __hip_atomic_store(ex + q, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                else
-                    __hip_atomic_store(ex + q, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(ex + q, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             uint64_t mine = 0;
             uint32_t spins = 0;
