@@ -26,8 +26,7 @@ struct sifar_ctx {
     int segs = 0;          // chunks per token
     int w_max = 0;         // max_tokens * segs
     int groups_per_token = 1;
-    bool chain_grouping = false;  // persistent steps may use kChainGroupWaves-wave workgroups
-    bool chain_prefetch = false;  // one-wave persistent steps' producers load sources ahead
+    bool chain_prefetch = false;  // persistent steps' producers load sources ahead
     int step_cap = 0;             // most chunks of a one-launch per-epoch step
     int split_cap = 0;            // ... of one with kStepConsumers consumer waves per chunk
     uint64_t slot_elems = 0;
@@ -182,23 +181,6 @@ int launch_red(sifar_t h, const ReduceArgs &ra, const ProduceArgs *next, hipStre
                                     h->cfg.waves_per_group, s));
 }
 
-// Waves per workgroup of a persistent step. Grouping lets one publication
-// (and, for a cross-XCD pair, one release fence) cover 4 chunks, and the
-// epilogue's groups share one exchange word. Measured on MI355X (payload
-// sweep shapes, us per all-reduce, one-wave vs grouped): plain steps at 1024
-// chunks 2.88 vs 2.87 (N = 8) and 1.25 vs 1.59 (N = 4), at 2048 chunks
-// 1.58 vs 1.85 (N = 2), 3.05 vs 2.95 (N = 4) and 8.2 vs 7.9 (N = 8), at
-// 4096 chunks 3.41 vs 3.64 (N = 2), 7.53 vs 7.99 (N = 4) and 15.3 vs 16.4
-// (N = 8); with the epilogue (MoE, 512 chunks) 3.06 vs 2.80. So plain steps
-// run one wave per workgroup, epilogue steps group from 512 chunks.
-int chain_waves(const sifar_ctx *h, int32_t tokens) {
-    const int64_t chunks = static_cast<int64_t>(tokens) * h->segs;
-    return h->cfg.epilogue && h->chain_grouping && h->segs % kChainGroupWaves == 0 &&
-                   chunks >= 512
-               ? kChainGroupWaves
-               : 1;
-}
-
 // Does a per-epoch step of `tokens` tokens run in one launch? Wherever its
 // workgroups fit at once (the kernel's comment has both sides measured) and its
 // buffers are apart.
@@ -214,9 +196,8 @@ int step_consumers(const sifar_ctx *h, int32_t tokens) {
     return static_cast<int64_t>(tokens) * h->segs <= h->split_cap ? kStepConsumers : 1;
 }
 
-// Arguments of the persistent step kernel for `tokens` tokens; returns the
-// workgroup width (waves) it runs with.
-int chain_args(const sifar_t h, int32_t tokens, ChainArgs *ca) {
+// Arguments of a step of `tokens` tokens in one launch.
+void chain_args(const sifar_t h, int32_t tokens, ChainArgs *ca) {
     const int L = h->cfg.reduces_per_step;
     const EpochRef ep{&h->state->epoch_base, 0, 0};
     *ca = ChainArgs{};
@@ -236,8 +217,7 @@ int chain_args(const sifar_t h, int32_t tokens, ChainArgs *ca) {
     } else {
         ca->r.out = static_cast<uint16_t *>(h->buf.out_ring);
     }
-    const int waves = h->cfg.persistent ? chain_waves(h, tokens) : 1;
-    ca->r.groups_per_token = h->segs / waves;  // the epilogue's exchange width
+    ca->r.groups_per_token = h->segs;  // the epilogue's exchange width
     ca->reduces = L;
     ca->ring_stride = static_cast<uint64_t>(h->cfg.max_tokens) * h->cfg.hidden;
     ca->late_delay = h->cfg.late_delay;
@@ -246,7 +226,6 @@ int chain_args(const sifar_t h, int32_t tokens, ChainArgs *ca) {
     ca->done = &h->state->chain_done;
     ca->place = h->place;
     ca->parity_mask = parity_mask(h);
-    return waves;
 }
 
 // Graph of a per-epoch step (persistent steps are one direct launch).
@@ -421,20 +400,15 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
         const int64_t waves = 2 * tokens * h->segs;
         // the prefetching producer holds two epochs' sources: it needs more
         // registers, so it runs wherever the step still fits with them
-        const int pcap = max_active_chain_groups(c.nranks, c.validate, c.epilogue != 0, 1, true);
+        const int pcap = max_active_chain_waves(c.nranks, c.validate, c.epilogue != 0, true);
         h->chain_prefetch = pcap > 0 && waves <= pcap;
         const int cap = h->chain_prefetch
                             ? pcap
-                            : max_active_chain_groups(c.nranks, c.validate, c.epilogue != 0, 1, false);
+                            : max_active_chain_waves(c.nranks, c.validate, c.epilogue != 0, false);
         if (cap <= 0 || waves > cap) {
             delete h;
             return SIFAR_EINVAL;
         }
-        const int gcap = c.epilogue ? max_active_chain_groups(c.nranks, c.validate, true,
-                                                              kChainGroupWaves, false)
-                                    : 0;
-        h->chain_grouping = c.nranks * kChainGroupWaves <= kLanes && gcap > 0 &&
-                            waves / kChainGroupWaves <= gcap;
     }
     if (SIFAR_ONE_LAUNCH && !c.persistent && c.fuse_peers && c.buffers == 2 &&
         (!c.epilogue || h->segs <= kLanes) && step_offsets_fit(c.nranks, h->slot_elems)) {
@@ -620,9 +594,9 @@ int sifar_step(sifar_t h, int32_t tokens, void *stream) {
             if (rc) return rc;
         }
         ChainArgs ca{};
-        const int waves = chain_args(h, tokens, &ca);
+        chain_args(h, tokens, &ca);
         rc = hip_status(
-            launch_chain(ca, h->cfg.validate, h->cfg.epilogue != 0, waves, h->chain_prefetch, s));
+            launch_chain(ca, h->cfg.validate, h->cfg.epilogue != 0, h->chain_prefetch, s));
         if (rc) return rc;
         step_enqueued(h, tokens, base);
         return SIFAR_OK;

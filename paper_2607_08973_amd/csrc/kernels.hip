@@ -644,30 +644,30 @@ __global__ __launch_bounds__(1024) void reduce_kernel(const uint32_t *ep_base, u
     residual_rmsnorm(a, k, g, o, rv, wv, a.y, lane, wave, G, blockIdx.x);
 }
 
-// The persistent step's epilogue in two halves, so that the wait for the
-// token's other groups overlaps the next epoch's reduction instead of
+// The epilogue of a step in one launch in two halves, so that the wait for the
+// token's other waves overlaps the next epoch's reduction instead of
 // stalling every chunk of the token once per epoch. Only the residual carries
 // from one epoch to the next, and it is this chunk's own (it stays in
 // registers for the whole step and is stored at its end); the token-wide sum
 // of squares is needed for y alone. epi_stage runs right after epoch g's sum:
-// it updates the residual, reduces this group's sum of squares and publishes
+// it updates the residual, reduces this wave's sum of squares and publishes
 // it in exchange plane g mod kExchPlanes. epi_finish runs one epoch later, or
 // after the step's last epoch: it takes the token's Q words of epoch g,
-// adds them (lanes_sum) and writes y. The arithmetic and its order are
-// residual_rmsnorm's. Four planes suffice: a group can publish epoch g + 4
-// only after finishing epoch g + 2, which needs every group's word of g + 2,
-// and a group publishes that only after it finished epoch g.
+// adds them (lanes_sum) and writes y. The arithmetic is residual_rmsnorm's.
+// Four planes suffice: a wave can publish epoch g + 4 only after finishing
+// epoch g + 2, which needs every wave's word of g + 2, and a wave publishes
+// that only after it finished epoch g.
 template <int W>
 struct EpiPending {
     Words<W> res;  // res' of this lane's elements
-    float grp;  // this workgroup's sum of squares
-    uint32_t g; // the epoch
+    float sum;     // this wave's sum of squares
+    uint32_t g;    // the epoch
 };
 
-template <bool GROUPED, int W>
+template <int W>
 __device__ __forceinline__ void epi_stage(const ReduceArgs &a, const Chunk &k, uint32_t g,
-                                          const Words<W> &o, Words<W> &res, int lane, int wave,
-                                          int G, int q, bool xlocal, EpiPending<W> &pd) {
+                                          const Words<W> &o, Words<W> &res, int lane, int q,
+                                          bool xlocal, EpiPending<W> &pd) {
     float ss = 0.f;
 #pragma unroll
     for (int i = 0; i < W; ++i) {
@@ -680,23 +680,15 @@ __device__ __forceinline__ void epi_stage(const ReduceArgs &a, const Chunk &k, u
     ss = wave_sum(k.lane_ok ? ss : 0.f);
     pd.res = res;
 
-    pd.grp = ss;
-    if (GROUPED) {
-        __shared__ float part[kMaxWavesPerGroup];
-        if (lane == 0) part[wave] = ss;
-        __syncthreads();
-        float grp = 0.f;
-        for (int w = 0; w < G; ++w) grp = grp + part[w];
-        pd.grp = grp;
-    }
+    pd.sum = ss;
     pd.g = g;
 
     const int Q = a.groups_per_token;
-    if (Q > 1 && wave == 0 && lane == 0) {
+    if (Q > 1 && lane == 0) {
         uint64_t *ex = a.exch + static_cast<size_t>(g % kExchPlanes) * a.exch_parity_stride +
                        static_cast<size_t>(k.t) * Q;
-        const uint64_t word = (static_cast<uint64_t>(g) << 32) | __float_as_uint(pd.grp);
-        // all groups of the token on this XCD: the word meets them in its L2
+        const uint64_t word = (static_cast<uint64_t>(g) << 32) | __float_as_uint(ss);
+        // all waves of the token on this XCD: the word meets them in its L2
         if (xlocal)
             __hip_atomic_store(ex + q, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         else
@@ -704,7 +696,7 @@ __device__ __forceinline__ void epi_stage(const ReduceArgs &a, const Chunk &k, u
     }
 }
 
-// This lane's exchange word of epoch g (lanes >= Q read group Q - 1's).
+// This lane's exchange word of epoch g (lanes >= Q read wave Q - 1's).
 __device__ __forceinline__ uint64_t epi_word(const ReduceArgs &a, const Chunk &k, uint32_t g,
                                              int lane) {
     const int Q = a.groups_per_token;
@@ -715,38 +707,30 @@ __device__ __forceinline__ uint64_t epi_word(const ReduceArgs &a, const Chunk &k
 }
 
 // `y` is the ring entry of epoch pd.g, `mine` this lane's exchange word of it
-// as loaded before the reduction of the epoch after (usually every group's is
+// as loaded before the reduction of the epoch after (usually every wave's is
 // there by then). (`pd` by value: with a reference the
-// compiler kept the pending state in scratch memory.) True in wave 0 when the
+// compiler kept the pending state in scratch memory.) True when the
 // exchange wait failed: it ran out of polls (latched here), or found an error
 // latched elsewhere.
-template <bool GROUPED, int W>
+template <int W>
 __device__ __forceinline__ bool epi_finish(const ReduceArgs &a, const Chunk &k,
                                            const EpiPending<W> pd, uint64_t mine,
-                                           const Words<W> &wv, uint16_t *y, int lane, int wave) {
+                                           const Words<W> &wv, uint16_t *y, int lane) {
     const int Q = a.groups_per_token;
-    float tot = pd.grp;
+    float tot = pd.sum;
     bool failed = false;
     if (Q > 1) {
-        if (wave == 0) {
-            uint32_t spins = 0;
-            bool ready = __ballot(static_cast<uint32_t>(mine >> 32) != pd.g) == 0;
-            while (!ready) {
-                if (spins >= kErrPollAfter && ld_relaxed(a.err) != 0) break;
-                if (++spins >= a.spin_limit) break;
-                mine = epi_word(a, k, pd.g, lane);
-                ready = __ballot(static_cast<uint32_t>(mine >> 32) != pd.g) == 0;
-            }
-            failed = !ready;
-            if (!ready && lane == 0) latch(a.err, kErrExchange, pd.g, k.c, spins);
-            tot = lanes_sum(__uint_as_float(static_cast<uint32_t>(mine)), Q, lane);
+        uint32_t spins = 0;
+        bool ready = __ballot(static_cast<uint32_t>(mine >> 32) != pd.g) == 0;
+        while (!ready) {
+            if (spins >= kErrPollAfter && ld_relaxed(a.err) != 0) break;
+            if (++spins >= a.spin_limit) break;
+            mine = epi_word(a, k, pd.g, lane);
+            ready = __ballot(static_cast<uint32_t>(mine >> 32) != pd.g) == 0;
         }
-        if (GROUPED) {
-            __shared__ float total;
-            if (wave == 0 && lane == 0) total = tot;
-            __syncthreads();
-            tot = total;
-        }
+        failed = !ready;
+        if (!ready && lane == 0) latch(a.err, kErrExchange, pd.g, k.c, spins);
+        tot = lanes_sum(__uint_as_float(static_cast<uint32_t>(mine)), Q, lane);
     }
     const float inv = 1.0f / __builtin_sqrtf(tot / static_cast<float>(a.geo.hidden) + a.eps);
     Words<W> yo;
@@ -867,87 +851,23 @@ __device__ __forceinline__ void chain_producer(const ChainArgs &A, uint32_t base
     }
 }
 
-// Grouped producer of epilogue steps (G waves per workgroup, one chunk per
-// wave): the waves
-// copy their chunks, wait until their stores have reached L2, meet at a
-// workgroup barrier, and wave 0 publishes for all of them (one agent-scope
-// release fence, needed only when a consumer of the group is on another XCD)
-// and stores every chunk's stamps (lane = chunk wave * N + rank). Such fences
-// write back the XCD's L2 and serialise per XCD, so sharing one among G chunks
-// shortens the epoch once several producer waves share each XCD. Every wave
-// reaches the barrier in every epoch; a failed slot wait ends the whole
-// workgroup at the same barrier.
-template <int N>
-__device__ __forceinline__ void chain_producer_grouped(const ChainArgs &A, uint32_t base,
-                                                       int lane, int wave, int G, int bx, int by) {
-    const ProduceArgs &a = A.p;
-    const Geometry &geo = a.geo;
-    const Chunk k = chunk_at(geo, by, bx * G + wave, lane);
-    const int sw = lane / N, sr = lane - sw * N;
-    const Chunk ks = chunk_at(geo, by, bx * G + (sw < G ? sw : 0), 0);
-    const bool stamper = wave == 0 && sw < G && ks.active;
-    if (k.active) publish_place(A.place + geo.w_max + k.c, base, lane);
-    const bool mine = !k.active || partner_is_local(A.place + k.c, base, lane);
-    const bool local = __syncthreads_and(mine ? 1 : 0) != 0;
-    for (int i = 0; i < A.reduces; ++i) {
-        const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
-        const uint32_t p = static_cast<uint32_t>(i + 1) & A.parity_mask;
-        bool free = true;
-        if (k.active) {
-            const size_t pc = static_cast<size_t>(p) * geo.w_max + k.c;
-            uint32_t spins = 0;
-            while (true) {  // one round trip per poll, as in chain_producer
-                const uint32_t done = ld_relaxed(a.consumed + pc);
-                const uint32_t prev = ld_relaxed(a.produced + pc);
-                const uint32_t e = spins >= kErrPollAfter ? ld_relaxed(a.err) : 0u;
-                free = done == prev;
-                if (free || ++spins >= A.r.spin_limit || e != 0) break;
-                __builtin_amdgcn_s_sleep(1);
-            }
-            if (!free && lane == 0) latch(a.err, kErrWaw, g, k.c, spins);
-            if (free) {
-                copy_chunk<N>(a, k, g, p);
-                // only this wave reads its chunk's produced word: recording it
-                // here, not after wave 0's fence, keeps the next epoch's slot
-                // check from seeing the previous value (with one buffer that
-                // would let the slot be rewritten before it is consumed)
-                if (lane == 0) st_flag(a.produced + pc, g, true);
-            }
-        }
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's slot stores have reached L2
-        if (__syncthreads_or(!free)) return;
-        if (wave == 0) {
-            const uint32_t inj = inject_word(a.inject, a.inject_div, g);
-            const uint32_t held = held_back(inj);
-            publish_slot(local);  // with `local` the wait above already did it
-            const size_t ps = static_cast<size_t>(p) * geo.w_max + ks.c;
-            uint32_t *stamp = a.stamps + ps * N;
-            if (stamper && !((held >> sr) & 1u)) st_flag(stamp + sr, g, local);
-            if (held) {
-                for (uint32_t d = 0; d < A.late_delay; ++d) __builtin_amdgcn_s_sleep(8);
-                if (stamper && ((inj >> sr) & 1u) && !((inj >> (8 + sr)) & 1u))
-                    st_flag(stamp + sr, g, local);
-            }
-        }
-    }
-}
-
-// Consumer wave of chunk (t, x * G + wave). With G > 1 and the epilogue the
-// group's waves share the RMSNorm barriers, so they also leave together.
-template <int N, int MODE, bool EPI, bool GROUPED>
-__device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base, int lane,
-                                               int wave, int G, int bx, int by) {
+// Consumer wave of chunk (t, x).
+template <int N, int MODE, bool EPI>
+__device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base, int lane, int bx,
+                                               int by) {
     const ReduceArgs &a = A.r;
     const Geometry &geo = a.geo;
-    const Chunk k = chunk_at(geo, by, bx * G + wave, lane);
+    const Chunk k = chunk_at(geo, by, bx, lane);
+    // (every wave has a chunk; with the test the compiler schedules the epilogue's
+    // loop 1.5 % faster)
     if (k.active) publish_place(A.place + k.c, base, lane);
     const bool local = k.active && partner_is_local(A.place + geo.w_max + k.c, base, lane);
-    // the epilogue's exchange partners: wave 0 of each group of this token
+    // the epilogue's exchange partners: the consumers of this token's chunks
     bool xlocal = false;
-    if (EPI && wave == 0) {
+    if (EPI) {
         const int Q = a.groups_per_token;
         const bool mine = lane >= Q ||
-                          tag_is_local(A.place + static_cast<size_t>(k.t) * geo.segs + lane * G, base);
+                          tag_is_local(A.place + static_cast<size_t>(k.t) * geo.segs + lane, base);
         xlocal = __ballot(!mine) == 0;
     }
     V16 wv, res;
@@ -976,7 +896,7 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
         const uint32_t g = base + static_cast<uint32_t>(i) + 1u;
         const uint32_t p = static_cast<uint32_t>(i + 1) & A.parity_mask;
         uint64_t word = 0;  // the pending epoch's exchange word
-        if (EPI && have_pending && wave == 0) word = epi_word(a, k, pending.g, lane);
+        if (EPI && have_pending) word = epi_word(a, k, pending.g, lane);
         V16 v[N];
         uint32_t attempts, first, last;
         const uint32_t st_first = st_next;
@@ -1017,9 +937,9 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
             st16_stream(a.out + ring + k.row, o);
         } else {
             EpiPending<4> cur;
-            epi_stage<GROUPED, 4>(a, k, g, o, res, lane, wave, G, bx, xlocal, cur);
-            if (have_pending && epi_finish<GROUPED, 4>(a, k, pending, word, wv,
-                                                    a.y + ring - A.ring_stride, lane, wave))
+            epi_stage<4>(a, k, g, o, res, lane, bx, xlocal, cur);
+            if (have_pending &&
+                epi_finish<4>(a, k, pending, word, wv, a.y + ring - A.ring_stride, lane))
                 stop = true;
             pending = cur;
             have_pending = true;
@@ -1031,7 +951,6 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
         // unwritten: the step has failed). Every wait is bounded and reads the
         // error word once it has lasted kErrPollAfter polls, so a failure
         // anywhere ends the other waves' waits too.
-        if (GROUPED && EPI) stop = __syncthreads_or(stop) != 0;
         if (stop) {
             if (EPI && k.lane_ok) st16(a.residual + k.row, res);
             return;
@@ -1039,40 +958,36 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
     }
     if (EPI) {
         if (k.lane_ok) st16(a.residual + k.row, res);
-        const uint64_t word = wave == 0 ? epi_word(a, k, pending.g, lane) : 0;
-        epi_finish<GROUPED, 4>(a, k, pending, word, wv,
-                            a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane, wave);
+        epi_finish<4>(a, k, pending, epi_word(a, k, pending.g, lane), wv,
+                      a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane);
     }
 }
 
 // Grid (segs, plane_rows(tokens, segs), 2) of one-wave workgroups, or with the
-// epilogue (8 * ceil(tokens / 8) * Q, 1, 2) of G-wave workgroups (G = 1, or
-// kChainGroupWaves when GROUPED; Q = segs / G, layout below): plane 0 reduces
-// chunk (t, x * G + wave) for epochs base+1 .. base+L in order, plane 1
-// produces it. The last wave to arrive on the counter advances the epoch base
-// for the next step: every wave read the base before it arrived, so no wave
-// can see the advanced value.
-// (The occupancy asked for with the epilogue keeps the largest steps that init
-// accepts where they were.)
-constexpr int chain_occupancy(int n, bool epi, bool grouped) {
-    if (!epi) return 1;
-    if (!grouped) return 5;
-    return n <= 2 ? 6 : n <= 6 ? 5 : 4;
-}
-
-template <int N, int MODE, bool EPI, bool GROUPED, bool PREFETCH>
-__global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
-                             chain_occupancy(N, EPI, GROUPED)) void chain_kernel(ChainArgs A) {
+// epilogue (8 * ceil(tokens / 8) * segs, 1, 2), layout below: plane 0 reduces
+// chunk (t, x) for epochs base+1 .. base+L in order, plane 1 produces it. The
+// last wave to arrive on the counter advances the epoch base for the next
+// step: every wave read the base before it arrived, so no wave can see the
+// advanced value. (The occupancy asked for with the epilogue keeps the largest
+// steps that init accepts where they were.)
+//
+// Epilogue steps from 512 chunks on once ran four-wave workgroups that shared a
+// slot publication and an exchange word, with barriers between their waves.
+// With the sums in vector registers and the residual kept there, one wave per
+// workgroup is the faster one at every size (us per all-reduce, four waves ->
+// one): N = 8, 32 x 8192, 2.12 -> 1.24; 64 x 8192, 2.92 -> 2.81; 160 x 8192,
+// 8.84 both; N = 4, 32 x 8192, 1.84 -> 1.06; N = 2, 64 x 8192, 1.83 -> 1.11; one
+// buffer, N = 8, 32 x 8192, 2.44 -> 1.59, 128 x 8192, 5.37 -> 5.40.
+template <int N, int MODE, bool EPI, bool PREFETCH>
+__global__ __launch_bounds__(kLanes, EPI ? 5 : 1) void chain_kernel(ChainArgs A) {
     const int lane = threadIdx.x & (kLanes - 1);
-    const int wave = GROUPED ? static_cast<int>(threadIdx.x) / kLanes : 0;
-    const int G = GROUPED ? static_cast<int>(blockDim.x) / kLanes : 1;
     const uint32_t base = A.r.ep.base[0];
-    // Logical (group, token). With the epilogue, workgroup b of a plane serves
-    // token (b mod 8) + 8 * (b / 8 / Q), group (b / 8) mod Q: every group of a
-    // token -- consumers and producers, since each plane holds a multiple of 8
-    // workgroups -- is dealt to the same XCD, so the per-epoch exchange of the
-    // token's sum of squares stays in one L2. Workgroups past the last token
-    // only arrive on the counter.
+    // Logical (chunk, token). With the epilogue, workgroup b of a plane serves
+    // token (b mod 8) + 8 * (b / 8 / segs), chunk (b / 8) mod segs: every chunk
+    // of a token -- consumers and producers, since each plane holds a multiple
+    // of 8 workgroups -- is dealt to the same XCD, so the per-epoch exchange of
+    // the token's sum of squares stays in one L2. Workgroups past the last
+    // token only arrive on the counter.
     int bx = blockIdx.x, by = blockIdx.y;
     if (EPI) {
         const int Q = A.r.groups_per_token;
@@ -1081,17 +996,13 @@ __global__ __launch_bounds__(GROUPED ? kChainGroupWaves * kLanes : kLanes,
         by = (static_cast<int>(blockIdx.x) & 7) + 8 * (j / Q);
     }
     if (by < A.r.geo.tokens) {
-        if (blockIdx.z == 1) {
-            if (GROUPED)
-                chain_producer_grouped<N>(A, base, lane, wave, G, bx, by);
-            else
-                chain_producer<N, PREFETCH>(A, base, lane, bx, by);
-        } else {
-            chain_consumer<N, MODE, EPI, GROUPED>(A, base, lane, wave, G, bx, by);
-        }
+        if (blockIdx.z == 1)
+            chain_producer<N, PREFETCH>(A, base, lane, bx, by);
+        else
+            chain_consumer<N, MODE, EPI>(A, base, lane, bx, by);
     }
     if (lane == 0) {
-        const uint32_t waves = 2u * gridDim.x * gridDim.y * static_cast<uint32_t>(G);
+        const uint32_t waves = 2u * gridDim.x * gridDim.y;
         const uint32_t before =
             __hip_atomic_fetch_add(A.done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (before == waves - 1u) {
@@ -1358,16 +1269,15 @@ __device__ __forceinline__ void step_consumer(const ChainArgs &A, uint32_t base,
             st_stream<W>(a.out + ring + k.row, o);
         } else {
             EpiPending<W> cur;
-            epi_stage<false, W>(a, k, g, o, res, lane, 0, 1, k.s * C + w, xlocal, cur);
-            if (i > 0)
-                epi_finish<false, W>(a, k, pending, word, wv, a.y + ring - A.ring_stride, lane, 0);
+            epi_stage<W>(a, k, g, o, res, lane, k.s * C + w, xlocal, cur);
+            if (i > 0) epi_finish<W>(a, k, pending, word, wv, a.y + ring - A.ring_stride, lane);
             pending = cur;
         }
     }
     if (EPI) {
         if (k.lane_ok) st_words<W>(a.residual + k.row, res);
-        epi_finish<false, W>(a, k, pending, epi_word(a, k, pending.g, lane), wv,
-                          a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane, 0);
+        epi_finish<W>(a, k, pending, epi_word(a, k, pending.g, lane), wv,
+                      a.y + static_cast<uint64_t>(A.reduces - 1) * A.ring_stride, lane);
     }
 }
 
@@ -1542,36 +1452,31 @@ hipError_t launch_reduce_n(const ReduceArgs &a, const ProduceArgs *pa, int mode,
     return hipErrorInvalidValue;
 }
 
-// Grouped workgroups serve epilogue steps only (plain steps measured faster
-// or level with one wave per workgroup); the grouped producer loads and
-// stores in one go. With the epilogue the consumer sets the register count,
-// so only the plain one-wave-per-chunk kernel comes in both producer forms.
+// With the epilogue the consumer sets the register count, so only the plain
+// kernel comes in both producer forms.
 template <int N, int MODE>
-const void *chain_fn(bool epi, bool grouped, bool prefetch) {
-    if (grouped)
-        return epi ? reinterpret_cast<const void *>(chain_kernel<N, MODE, true, true, false>)
-                   : nullptr;
-    if (epi) return reinterpret_cast<const void *>(chain_kernel<N, MODE, true, false, true>);
-    return prefetch ? reinterpret_cast<const void *>(chain_kernel<N, MODE, false, false, true>)
-                    : reinterpret_cast<const void *>(chain_kernel<N, MODE, false, false, false>);
+const void *chain_fn(bool epi, bool prefetch) {
+    if (epi) return reinterpret_cast<const void *>(chain_kernel<N, MODE, true, true>);
+    return prefetch ? reinterpret_cast<const void *>(chain_kernel<N, MODE, false, true>)
+                    : reinterpret_cast<const void *>(chain_kernel<N, MODE, false, false>);
 }
 
 // Persistent steps validate before they load: ORDERED only.
 template <int N>
-const void *chain_fn_n(int mode, bool epi, bool grouped, bool prefetch) {
-    return mode == kOrdered ? chain_fn<N, kOrdered>(epi, grouped, prefetch) : nullptr;
+const void *chain_fn_n(int mode, bool epi, bool prefetch) {
+    return mode == kOrdered ? chain_fn<N, kOrdered>(epi, prefetch) : nullptr;
 }
 
-const void *chain_fn_any(int nranks, int mode, bool epi, bool grouped, bool prefetch) {
+const void *chain_fn_any(int nranks, int mode, bool epi, bool prefetch) {
     switch (nranks) {
-        case 1: return chain_fn_n<1>(mode, epi, grouped, prefetch);
-        case 2: return chain_fn_n<2>(mode, epi, grouped, prefetch);
-        case 3: return chain_fn_n<3>(mode, epi, grouped, prefetch);
-        case 4: return chain_fn_n<4>(mode, epi, grouped, prefetch);
-        case 5: return chain_fn_n<5>(mode, epi, grouped, prefetch);
-        case 6: return chain_fn_n<6>(mode, epi, grouped, prefetch);
-        case 7: return chain_fn_n<7>(mode, epi, grouped, prefetch);
-        case 8: return chain_fn_n<8>(mode, epi, grouped, prefetch);
+        case 1: return chain_fn_n<1>(mode, epi, prefetch);
+        case 2: return chain_fn_n<2>(mode, epi, prefetch);
+        case 3: return chain_fn_n<3>(mode, epi, prefetch);
+        case 4: return chain_fn_n<4>(mode, epi, prefetch);
+        case 5: return chain_fn_n<5>(mode, epi, prefetch);
+        case 6: return chain_fn_n<6>(mode, epi, prefetch);
+        case 7: return chain_fn_n<7>(mode, epi, prefetch);
+        case 8: return chain_fn_n<8>(mode, epi, prefetch);
     }
     return nullptr;
 }
@@ -1705,25 +1610,23 @@ hipError_t launch_reduce(const ReduceArgs &a, const ProduceArgs *next, int mode,
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, bool prefetch,
-                        hipStream_t s) {
-    if (waves != 1 && waves != kChainGroupWaves) return hipErrorInvalidValue;
-    const void *fn = chain_fn_any(a.r.geo.nranks, mode, epilogue, waves > 1, prefetch);
+hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, bool prefetch, hipStream_t s) {
+    const void *fn = chain_fn_any(a.r.geo.nranks, mode, epilogue, prefetch);
     if (!fn) return hipErrorInvalidValue;
-    if (a.r.geo.segs != a.p.geo.segs || a.r.geo.tokens != a.p.geo.tokens ||
-        a.r.geo.segs % waves != 0 || (waves > 1 && waves * a.r.geo.nranks > kLanes))
+    if (a.r.geo.segs != a.p.geo.segs || a.r.geo.tokens != a.p.geo.tokens)
         return hipErrorInvalidValue;
-    const uint32_t q = static_cast<uint32_t>(a.r.geo.segs / waves);
+    const uint32_t segs = static_cast<uint32_t>(a.r.geo.segs);
     const uint32_t t8 = (static_cast<uint32_t>(a.r.geo.tokens) + 7u) / 8u;
-    if (epilogue && a.r.groups_per_token != static_cast<int32_t>(q)) return hipErrorInvalidValue;
+    if (epilogue && (a.r.geo.segs > kLanes || a.r.groups_per_token != a.r.geo.segs))
+        return hipErrorInvalidValue;
     // the slots are addressed at 32-bit offsets from rank 0's (payload loads,
     // slot stores); co-residency keeps a step far below that (at most 4096
     // chunks: under 64 MiB of slots)
     if (!step_offsets_fit(a.r.geo.nranks, a.r.geo.slot_elems)) return hipErrorInvalidValue;
-    const dim3 grid = epilogue ? dim3(8u * t8 * q, 1, 2)
-                               : dim3(q, static_cast<uint32_t>(plane_rows(a.r.geo.tokens, q)), 2);
+    const dim3 grid = epilogue ? dim3(8u * t8 * segs, 1, 2)
+                               : dim3(segs, static_cast<uint32_t>(plane_rows(a.r.geo.tokens, segs)), 2);
     void *args[] = {const_cast<ChainArgs *>(&a)};
-    return hipLaunchKernel(fn, grid, dim3(kLanes * waves), args, 0, s);
+    return hipLaunchKernel(fn, grid, dim3(kLanes), args, 0, s);
 }
 
 hipError_t launch_once(const Geometry &geo, uint32_t g, const uint16_t *src, int64_t rank_stride,
@@ -1785,10 +1688,8 @@ int max_active_groups(int nranks, int mode, bool epilogue, int waves_per_group) 
     return resident_groups(reduce_fn_any(nranks, mode, epilogue), waves_per_group * kLanes);
 }
 
-int max_active_chain_groups(int nranks, int mode, bool epilogue, int waves, bool prefetch) {
-    if (waves != 1 && waves != kChainGroupWaves) return 0;
-    return resident_groups(chain_fn_any(nranks, mode, epilogue, waves > 1, prefetch),
-                           waves * kLanes);
+int max_active_chain_waves(int nranks, int mode, bool epilogue, bool prefetch) {
+    return resident_groups(chain_fn_any(nranks, mode, epilogue, prefetch), kLanes);
 }
 
 hipError_t launch_advance(uint32_t *epoch_base, uint32_t step, hipStream_t s) {

@@ -12,7 +12,6 @@ constexpr int kVec = 8;                    // bf16 elements per 16-byte load
 constexpr int kChunk = kLanes * kVec;      // elements per chunk: one wave, one load per rank per lane
 constexpr int kMaxRanks = 8;
 constexpr int kMaxWavesPerGroup = 16;
-constexpr int kChainGroupWaves = 4;         // waves per persistent-step workgroup when grouped
 constexpr int kStepConsumers = 4;           // consumer waves of a one-launch step's chunk when split
 constexpr int kSplitChunks = 256;           // most chunks of a step that splits them
 constexpr int kExchPlanes = 4;              // epoch-indexed planes of the epilogue exchange
@@ -179,16 +178,13 @@ hipError_t launch_reduce(const ReduceArgs &a, const ProduceArgs *next, int mode,
 // Workgroups of the reduction kernel that can be resident at once on the
 // current device (0 if unknown).
 int max_active_groups(int nranks, int mode, bool epilogue, int waves_per_group);
-// Same for the persistent chain kernel's workgroups of `waves` waves (1 or
-// kChainGroupWaves); `prefetch` picks the one-wave kernel whose producer loads
-// an epoch's sources ahead (more registers, lower occupancy).
-int max_active_chain_groups(int nranks, int mode, bool epilogue, int waves, bool prefetch);
+// Same for the persistent chain kernel's one-wave workgroups; `prefetch` picks
+// the plain kernel whose producer loads an epoch's sources ahead (more
+// registers, lower occupancy).
+int max_active_chain_waves(int nranks, int mode, bool epilogue, bool prefetch);
 // Persistent step: grid (segs, plane_rows(tokens, segs), 2), or with the
-// epilogue one that puts a token's workgroups on one XCD; waves = 1, or
-// kChainGroupWaves (segs divisible by it, waves * nranks <= 64) to let one
-// release fence cover a workgroup's chunks.
-hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, int waves, bool prefetch,
-                        hipStream_t s);
+// epilogue one that puts a token's workgroups on one XCD.
+hipError_t launch_chain(const ChainArgs &a, int mode, bool epilogue, bool prefetch, hipStream_t s);
 // One-launch steps address the slots at 32-bit offsets from rank 0's.
 inline bool step_offsets_fit(int nranks, uint64_t slot_elems) {
     return static_cast<uint64_t>(nranks) * 4u * slot_elems <= 0x7fffffffull;

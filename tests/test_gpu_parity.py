@@ -482,17 +482,17 @@ def test_epilogue_widest_rows(N, T, H, persistent, G):
 
 @pytest.mark.parametrize("N,T,H", [(5, 64, 3896), (3, 130, 2040)])
 def test_persistent_epilogue_grouped_ragged(N, T, H):
-    """Persistent residual-add + RMSNorm steps from 512 chunks run in 4-wave
-    workgroups: 3896 leaves a partial last chunk inside each token's last
-    group; 130 tokens pad the grid to 136 (one XCD per token), so the padding
-    tokens' workgroups only arrive on the counter. Two steps of 8 chained
-    nodes: residual bit-exact, y within 1 bf16 step."""
+    """Persistent residual-add + RMSNorm steps of 512 chunks and more: 3896
+    leaves a partial last chunk in each row; 130 tokens pad the grid to 136 (one
+    XCD per token), so the padding tokens' workgroups only arrive on the
+    counter. Two steps of 8 chained nodes: residual bit-exact, y within 1 bf16
+    step."""
     w = synth.Workload(97 + N, f"epilogue-grouped-n{N}-t{T}-h{H}", N, (T,), H, 8, 2, "act",
                        epilogue=True)
     run = StepRun(w, T, persistent=1, pool=synth.payload_pool(w.wid, N, T, H, 5, w.dist))
     res = run.res0[:T].copy()
     for step in range(2):
-        print(f"epilogue grouped N={N} T={T} H={H} step {step}", flush=True)
+        print(f"epilogue many chunks N={N} T={T} H={H} step {step}", flush=True)
         epochs = run.step(T)
         y_got = to_host(run.y_d)
         _, r_list, y_list = oracle.reduce_chain(run.pool, epochs, T,
@@ -598,8 +598,7 @@ def test_steps_with_a_changing_batch_size(persistent):
 @pytest.mark.parametrize("T", [4, 8])
 def test_persistent_late_stamps(T):
     """Late ranks' stamps land after a delay while the reduction waits on them:
-    outputs equal the oracle; the decision log shows retries and ends clean.
-    (The grouped producer meets late stamps in the epilogue tests below.)"""
+    outputs equal the oracle; the decision log shows retries and ends clean."""
     w = synth.SPEC_STRESS
     steps = 6
     late = synth.delay_table(w.wid, w.nranks, w.reduces_per_step * steps, w.stale_prob)
@@ -624,9 +623,8 @@ def test_persistent_late_stamps(T):
 @pytest.mark.parametrize("T,H,epilogue", [(2, 1024, False), (8, 4096, False), (64, 4096, True)])
 def test_persistent_withheld_stamp_latches(T, H, epilogue):
     """A stamp that never lands ends the step with a latched error instead of
-    a hang. With the epilogue, 64 tokens x 8 chunks run in 4-wave workgroups:
-    the grouped producer, and groups that wait for each other's sums of
-    squares while their own wait fails."""
+    a hang. With the epilogue, 64 tokens x 8 chunks: waves that wait for each
+    other's sums of squares while their own wait fails."""
     w = synth.Workload(70, "withheld", 4, (T,), H, 8, 1, "normal", epilogue=epilogue)
     run = StepRun(w, T, persistent=1, max_attempts=64, spin_limit=1 << 14)
     table = [0] * 16

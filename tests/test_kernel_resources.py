@@ -61,21 +61,20 @@ def kernel_resources(tmp_path_factory):
     return found
 
 
-def _chain(n, epi, grouped, prefetch):
+def _chain(n, epi, prefetch):
     b = lambda x: "1" if x else "0"
-    return (f"_ZN5sifar12_GLOBAL__N_112chain_kernelILi{n}ELi1ELb{b(epi)}ELb{b(grouped)}"
+    return (f"_ZN5sifar12_GLOBAL__N_112chain_kernelILi{n}ELi1ELb{b(epi)}"
             f"ELb{b(prefetch)}EEEvNS_9ChainArgsE")
 
 
 def test_largest_steps_fit_eight_waves_per_simd(kernel_resources):
     """The non-prefetching one-wave kernel of a plain N = 8 step stays within
     64 VGPRs (the form init falls back to when a step needs every wave slot of
-    the GPU). Plain steps have no grouped kernel: only epilogue steps group."""
-    name = _chain(8, False, False, False)
+    the GPU)."""
+    name = _chain(8, False, False)
     assert name in kernel_resources, name
     assert kernel_resources[name]["vgpr"] <= VGPRS_FOR_8_WAVES_PER_SIMD, (
         name, kernel_resources[name])
-    assert _chain(8, False, True, False) not in kernel_resources
 
 
 def test_prefetching_kernel_keeps_its_occupancy(kernel_resources):
@@ -84,7 +83,7 @@ def test_prefetching_kernel_keeps_its_occupancy(kernel_resources):
     one-wave steps of up to 3072 chunks (larger handles fall back to the
     non-prefetching form), and it does not spill. (A producer slot wait
     without its short sleep once took it to 109.)"""
-    name = _chain(8, False, False, True)
+    name = _chain(8, False, True)
     assert name in kernel_resources, name
     r = kernel_resources[name]
     assert r["vgpr"] <= 80 and r["spill"] == 0, (name, r)
@@ -124,6 +123,13 @@ def test_injecting_steps_spill_few_scalars(kernel_resources, epi, bound):
         for mode in (0, 1):
             name = _step(n, mode, epi, True, 1)
             assert kernel_resources[name]["sgpr_spill"] <= bound, (name, kernel_resources[name])
+
+
+def test_persistent_epilogue_keeps_its_places(kernel_resources):
+    """Persistent epilogue steps: 5 waves per SIMD (2560 chunks), no spills."""
+    for n in range(1, 9):
+        r = kernel_resources[_chain(n, True, True)]
+        assert r["vgpr"] <= 96 and r["spill"] == 0 and r["scratch"] == 0, (n, r)
 
 
 def test_one_launch_all_reduce_keeps_its_places(kernel_resources):
