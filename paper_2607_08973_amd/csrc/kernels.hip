@@ -364,11 +364,14 @@ __device__ __forceinline__ uint32_t gather(const ReduceArgs &a, const Chunk &k, 
 // found while waiting. With AT the payload loads share one descriptor, every
 // rank at a scalar offset, and leave back to back (a lone wave pays an issue
 // slot for every instruction: three scalar ones per descriptor kept the last
-// load ~50 ns behind the first). Epilogue kernels keep a descriptor per load:
-// their scalar registers are full, and the hoisted offsets spilled into 12
-// more vector registers. Measured with the producer's stores done the same
-// way (llama8b decode, us per all-reduce): 0.759 -> 0.721 at T = 1..8,
-// 0.80 -> 0.75 at 16 tokens, 1.13 -> 1.08 at 64 tokens.
+// load ~50 ns behind the first). Measured with the producer's stores done the
+// same way (llama8b decode, us per all-reduce): 0.759 -> 0.721 at T = 1..8,
+// 0.80 -> 0.75 at 16 tokens, 1.13 -> 1.08 at 64 tokens. With the epilogue, whose
+// scalar registers are full, it is the faster one from five ranks (8 x 8192,
+// descriptor per load -> one: N = 5 1.020 -> 1.012, N = 6 1.060 -> 1.038, N = 8
+// 1.083 -> 1.068; N = 8, 64 x 8192, 2.73 -> 2.70; N = 8, 128 x 8192, 7.02 -> 6.96)
+// and mostly the slower one below (N = 4 0.953 -> 0.971, N = 2 0.908 -> 0.921,
+// N = 3 0.964 -> 0.954), so that is the line.
 template <int N, bool AT>
 __device__ __forceinline__ bool gather_chain(const ReduceArgs &a, const Chunk &k, uint32_t g,
                                              uint32_t p, int lane, uint32_t m, uint32_t &st,
@@ -902,7 +905,7 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
         const uint32_t st_first = st_next;
         uint32_t st_last = st_next;
         bool stop =
-            gather_chain<N, !EPI>(a, k, g, p, lane, m_next, st_last, v, attempts, first, last, local);
+            gather_chain<N, !EPI || (N > 4)>(a, k, g, p, lane, m_next, st_last, v, attempts, first, last, local);
         uint32_t *consumed = a.consumed + static_cast<size_t>(p) * geo.w_max + k.c;
         // Once the payload has arrived: issue the next epoch's first poll (a
         // harmless in-bounds read after the last epoch), then release the slot
@@ -915,8 +918,9 @@ __device__ __forceinline__ void chain_consumer(const ChainArgs &A, uint32_t base
         };
         if (!EPI) {
             // release the slot as soon as every payload load has returned (the
-            // sum works on registers); measured faster for the plain chain,
-            // slower with the epilogue
+            // sum works on registers); with the epilogue that is the slower one
+            // (N = 8, 8 x 8192: 1.18 us per all-reduce, after the sum 1.10; N =
+            // 2, 64 x 8192: 1.13 and 1.12)
 #pragma unroll
             for (int r = 0; r < N; ++r) complete(v[r]);
             poll_next_and_release();
@@ -1032,13 +1036,15 @@ __global__ __launch_bounds__(kLanes, EPI ? 5 : 1) void chain_kernel(ChainArgs A)
 // the issue of its stores; from 1024 chunks at N = 8 the bytes. Measured
 // against one launch per all-reduce (us per all-reduce, launches -> one
 // launch, one consumer wave): N = 8, 4 tokens x 4096, 64 per step, 2.62 ->
-// 0.58; with 10 % late stamps 3.70 -> 1.16; 20 per step: N = 2, 1 x 4096, 2.59 -> 0.49; N = 8, 64 x
-// 4096, 3.69 -> 1.14; 64 x 8192, 5.49 -> 3.04; 256 x 8192 (4096 chunks, every
-// wave slot of the GPU), 16.3 -> 14.0; N = 2, 256 x 8192, 6.46 -> 3.92. With
-// the epilogue: 1 x 4096, 4.57 -> 1.13; 40 x 8192, 7.21 -> 1.71; 32 x 8192 with
-// 5 % late stamps, 120 per step, 10.6 -> 1.72. It is the faster one wherever its
-// workgroups fit at once, so that is the rule; beyond that, chunks would run
-// their whole step one after another, which no sequence of all-reduces does.
+// 0.58; with 10 % late stamps 3.70 -> 1.12; 20 per step: N = 2, 1 x 4096, 2.59
+// -> 0.49; N = 8, 64 x 4096, 3.69 -> 1.14; 64 x 8192, 5.49 -> 3.04; 256 x 8192
+// (4096 chunks, every wave slot of the GPU), 16.3 -> 14.0; N = 2, 256 x 8192,
+// 6.46 -> 3.92. With the epilogue: 1 x 4096, 4.57 -> 1.13; 40 x 8192, 7.21 ->
+// 1.71; 32 x 8192 with 5 % late stamps, 120 per step, 10.6 -> 1.68. It is the
+// faster one wherever its workgroups fit at once, so that is the rule (with the
+// epilogue up to a quarter of that, see sifar_init); beyond that, chunks would
+// run their whole step one after another, which no sequence of all-reduces
+// does.
 // INJECT: the kernel that knows the injection table; without one the table's
 // branches leave the scalar registers (and 5 % of the time).
 //
@@ -1324,7 +1330,7 @@ __global__ __launch_bounds__((C + 1) * kLanes, EPI ? 5 : 8) void step_kernel(Cha
 // they arrive and validates. What bounds it: one launch, a round trip for the
 // sources and one for the payload. As a producer and a reduction launch the
 // call took 10.9 us (N = 8, 16 tokens x 4096, calls back to back from Python),
-// 7.3 so, most of it the caller's.
+// 5.0 so, most of it the caller's.
 // The arguments up to the source loads lead, to be preloaded into scalar
 // registers; the epoch itself is one of them.
 template <int N>
