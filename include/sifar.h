@@ -138,7 +138,9 @@ typedef struct {
                                  waves_per_group hold a whole token: its launches would not
                                  wait at all) */
     int32_t log_epochs;       /* decision-log ring length, in epochs, >= 1 */
-    int32_t waves_per_group;  /* waves (64 lanes) per workgroup: 1, 2, 4, 8 or 16 */
+    int32_t waves_per_group;  /* waves (64 lanes) per workgroup of a launch per all-reduce
+                                 (eager calls, steps as graphs): 1, 2, 4, 8 or 16; steps in
+                                 one launch have workgroups of their own */
     int32_t fuse_peers;       /* per-epoch steps: 1 = while epoch g is reduced the peers write
                                  epoch g + 1 (other parity), see sifar_step; 0 = separate
                                  producer and reduction launches */
@@ -204,8 +206,8 @@ int sifar_reduce(sifar_t h, void *out, int32_t tokens, void *stream);
 int sifar_reduce_rmsnorm(sifar_t h, void *residual, const void *weight, void *y,
                          int32_t tokens, void *stream);
 
-/* ---- decode step: L chained all-reduces in one captured HIP graph -----------
- * Binds the caller-owned buffers a step graph uses (Sec. 6.1 times
+/* ---- decode step: L chained all-reduces in one launch or one HIP graph ------
+ * Binds the caller-owned buffers a step uses (Sec. 6.1 times
  * all-reduces back to back inside the forward pass; Sec. 3.5: a CUDA graph
  * or megakernel keeps the GPUs in lockstep). Rebinding drops captured graphs.
  *   src_pool      [pool_entries][N][...] bf16: epoch g's partials are entry
@@ -239,13 +241,14 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
  * epoch-counter advance. A per-epoch step with fuse_peers runs in phases:
  * produce(g1), then L-1 phases that each reduce g_i while the peers write
  * g_(i+1), then reduce(g_L). One whose buffers are apart and whose chunks all
- * fit the GPU at once as two-wave workgroups (4096 chunks on MI355X; with the epilogue, a quarter of
- * what fits, at least 640 chunks of at most 64 per token) is one kernel launch: a
- * workgroup is one chunk, its last wave the peers, the one (or, up to 256
- * chunks, four) before it the reduction, and a workgroup barrier separates the
- * phases. Any other is one
- * hipGraphLaunch of a kernel node per phase (L + 1); without fuse_peers, of
- * L x (produce, reduce). Outputs, logs and errors are the same either way (the
+ * fit the GPU at once as two-wave workgroups is one kernel launch: 4096 chunks
+ * on MI355X, or with the epilogue a quarter of what fits (640 to 1024 chunks by
+ * rank count and validation, of at most 64 chunks per token; sifar_step_plan
+ * says which). A workgroup is one chunk, its last wave the peers, the one (or,
+ * up to 256 chunks, four) before it the reduction, and a workgroup barrier
+ * separates the phases. Any other is one hipGraphLaunch of a kernel node per
+ * phase (L + 1); without fuse_peers, of L x (produce, reduce); the last node
+ * advances the epochs. Outputs, logs and errors are the same either way (the
  * epilogue's y within its tolerance).
  * A persistent step is one kernel launch for the whole
  * step (a one-node graph replay measured slower). In a persistent step the
@@ -253,9 +256,9 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
  * epoch before its stamps (the decision log records the polls: attempts and
  * the stale ranks of the first and last poll), and injected late stamps land
  * after late_delay instead of after the first failed validation.
- * A per-epoch step's graph for a token count is captured on first use (on a
+ * A step's graph for a token count is captured on first use (on a
  * library-owned stream) and replayed afterwards; epochs and parities come
- * from a device-resident counter, so neither a replay nor a persistent
+ * from a device-resident counter, so neither a replay nor a step in one
  * launch needs per-all-reduce host work. Requires no produced-but-unreduced
  * epoch (SIFAR_ESTATE).
  * Steps are not for recording into a caller's stream capture (the host counts
@@ -267,7 +270,11 @@ int sifar_bind_step(sifar_t h, const sifar_step_buffers *b);
  * A persistent step needs all its waves resident at once (checked at init
  * against an otherwise idle GPU); persistent steps of several handles that run
  * concurrently on different streams may not fit together, and then end with a
- * latched SIFAR_EDEVICE (every wait is bounded) instead of completing. Once one
+ * latched SIFAR_EDEVICE (every wait is bounded) instead of completing. A
+ * per-epoch step with the epilogue waits too, for the other chunks of its
+ * tokens: in one launch it takes at most a quarter of the GPU, so such steps of
+ * four handles fit at once; beside more, or beside other work that holds the
+ * GPU, a wait can outlast spin_limit polls and latch SIFAR_DEV_EXCHANGE. Once one
  * wave of a persistent step has latched an error, the others end within
  * microseconds: a wait that has lasted 64 polls also reads the error word. */
 int sifar_step(sifar_t h, int32_t tokens, void *stream);

@@ -416,7 +416,12 @@ int sifar_init(const sifar_config *cfg, sifar_t *out) {
         // With the epilogue a token's workgroups wait for each other. A
         // quarter of the GPU's places leaves room for the steps of three more
         // handles on other streams (a process has 4 hardware queues), which
-        // one launch per all-reduce could run beside each other.
+        // one launch per all-reduce could run beside each other. That costs
+        // the larger steps of a handle alone (us per all-reduce, launches as
+        // they are, one launch if it were allowed): N = 8, 48 x 8192, 6.40 and
+        // 1.81; 64 x 8192, 7.29 and 2.76; 160 x 8192 (every place) 13.1 and
+        // 8.61; N = 2, 64 x 8192, 5.34 and 1.11. Short of the line, N = 8,
+        // 40 x 8192 runs at 1.48.
         h->split_cap = max_active_split_step_groups(c.nranks, c.validate, c.epilogue != 0);
         if (c.epilogue) {
             h->step_cap /= 4;
