@@ -68,16 +68,6 @@ def produce_bytes(N: int, T: int, H: int) -> int:
     return 2 * N * K + 4 * N * chunks
 
 
-def step_launches(L: int, chunks: int, persistent, fused, epilogue=False) -> int:
-    """Kernel launches of one decode step: one for a persistent step and for a
-    per-epoch step with the peers one epoch ahead whose chunks fit the GPU as
-    two-wave workgroups (16 on each of 256 CUs; with the epilogue a quarter of
-    10)."""
-    if persistent or (fused and chunks <= (640 if epilogue else 4096)):
-        return 1
-    return L + 2 if fused else 2 * L + 1
-
-
 def latency_floors() -> dict:
     """The library's latency probes (sifar_floor): launch and graph-node
     floors, one agent-scope atomic, acquire / coherent / warm / cache-missing
@@ -354,7 +344,8 @@ def chain_point(w, T, args, *, T_max=None, pool_entries=None, inject=False, wave
     out = {"workload": w.name, "nranks": N, "tokens": T, "hidden": H, "chain": L,
            "steps": args.steps, "us_per_reduce": ms * 1e3 / (args.steps * L)}
     fused_launch = args.fuse and args.buffers == 2
-    launches = step_launches(L, T * ((H + 511) // 512), args.persistent, fused_launch, w.epilogue)
+    launches = s.step_plan(T)[0]
+    out["launches_per_step"] = launches
     out["launch_period_us"] = ms * 1e3 / (args.steps * launches)
     red = reduce_bytes(N, T, H) + (epilogue_bytes(T, H) if w.epilogue else 0)
     out["reduce_bytes"] = red
@@ -653,6 +644,8 @@ def suite(args):
                 p = chain_point(w, T, args, T_max=max(w.tokens), inject=True, waves_per_group=G)
                 p["waves_per_group"] = G
                 pts.append(p)
+                if p.get("launches_per_step", 1) == 1:
+                    break  # a step in one launch has workgroups of its own
     else:
         raise SystemExit(f"unknown workload {args.workload}")
     for p in pts:
@@ -764,7 +757,7 @@ def main():
     # N*K, write K, read the stamps); the emulated peers' copies (read N*K,
     # write N*K, write the stamps) are reported apart.
     fused = args.fuse and args.buffers == 2
-    one = step_launches(L, max(tokens) * ((H + 511) // 512), args.persistent, fused) == 1
+    one = s.step_plan(max(tokens))[0] == 1
     kern = kernel_table(per_t, tokens, N, H, L, one, fused)
     mean_period = sum(k["launch_period_us"] for k in kern.values()) / len(kern)
     mean_bytes = sum(k["bytes_per_launch"] for k in kern.values()) / len(kern)
