@@ -50,6 +50,47 @@ struct PerDevice {
 std::mutex g_mutex;
 PerDevice g_dev[kMaxDevices];
 
+// The same all-reduce as a launch of the peers and one of the reduction, for
+// outputs that overlap the sources. (Out of line: its argument blocks are large.)
+__attribute__((noinline)) hipError_t launch_apart(const Geometry &geo, uint32_t g,
+                                                  const uint16_t *src, int64_t rank_stride,
+                                                  uint16_t *slots, uint32_t *stamps,
+                                                  const uint32_t *zero, const OnceArgs &a,
+                                                  hipStream_t s) {
+    // the epoch is passed whole: base = the always-zero word
+    const EpochRef ep{zero, g, g & 1u};
+    ProduceArgs pa{};
+    pa.geo = geo;
+    pa.ep = ep;
+    pa.slots = slots;
+    pa.stamps = stamps;
+    pa.consumed = a.consumed;
+    pa.produced = a.produced;
+    pa.src = src;
+    pa.rank_stride = rank_stride;
+    pa.entries = 1;
+    pa.entries_div = make_div(1);
+    pa.inject_div = make_div(1);
+    pa.err = a.err;
+    ReduceArgs ra{};
+    ra.geo = geo;
+    ra.ep = ep;
+    ra.slots = slots;
+    ra.stamps = stamps;
+    ra.consumed = a.consumed;
+    ra.log = a.log;
+    ra.log_epochs = 1;
+    ra.log_div = make_div(1);
+    ra.inject_div = make_div(1);
+    ra.max_attempts = a.max_attempts;
+    ra.spin_limit = 1;
+    ra.out = a.out;
+    ra.groups_per_token = 1;
+    ra.err = a.err;
+    const hipError_t e = launch_produce(pa, 1, s);
+    return e == hipSuccess ? launch_reduce(ra, nullptr, kSpec, false, 1, s) : e;
+}
+
 }  // namespace
 }  // namespace sifar
 
@@ -106,41 +147,6 @@ extern "C" int sifar_allreduce_noalloc(const void *src, int64_t src_rank_stride,
     blocks.ranks = static_cast<uint64_t>(nranks);
     blocks.rank_bytes = static_cast<uint64_t>(src_rank_stride) * 2;
     blocks.block = bytes;
-    if (chunks_race(blocks, Span{reinterpret_cast<uintptr_t>(out), bytes})) {
-        // the epoch is passed whole: base = the always-zero word
-        const EpochRef ep{&state->zero, g, g & 1u};
-        ProduceArgs pa{};
-        pa.geo = geo;
-        pa.ep = ep;
-        pa.slots = slots;
-        pa.stamps = stamps;
-        pa.consumed = consumed;
-        pa.produced = produced;
-        pa.src = static_cast<const uint16_t *>(src);
-        pa.rank_stride = src_rank_stride;
-        pa.entries = 1;
-        pa.entries_div = make_div(1);
-        pa.inject_div = make_div(1);
-        pa.err = state->err;
-        ReduceArgs ra{};
-        ra.geo = geo;
-        ra.ep = ep;
-        ra.slots = slots;
-        ra.stamps = stamps;
-        ra.consumed = consumed;
-        ra.log = log;
-        ra.log_epochs = 1;
-        ra.log_div = make_div(1);
-        ra.inject_div = make_div(1);
-        ra.max_attempts = kAttempts;
-        ra.spin_limit = 1;
-        ra.out = static_cast<uint16_t *>(out);
-        ra.groups_per_token = 1;
-        ra.err = state->err;
-        if (launch_produce(pa, 1, s) != hipSuccess) return SIFAR_EHIP;
-        if (launch_reduce(ra, nullptr, kSpec, false, 1, s) != hipSuccess) return SIFAR_EHIP;
-        return SIFAR_OK;
-    }
     OnceArgs a{};
     a.consumed = consumed;
     a.produced = produced;
@@ -148,8 +154,11 @@ extern "C" int sifar_allreduce_noalloc(const void *src, int64_t src_rank_stride,
     a.out = static_cast<uint16_t *>(out);
     a.max_attempts = kAttempts;
     a.err = state->err;
-    if (launch_once(geo, g, static_cast<const uint16_t *>(src), src_rank_stride, slots, stamps, a,
-                    s) != hipSuccess)
-        return SIFAR_EHIP;
-    return SIFAR_OK;
+    const bool race = chunks_race(blocks, Span{reinterpret_cast<uintptr_t>(out), bytes});
+    const hipError_t e =
+        race ? launch_apart(geo, g, static_cast<const uint16_t *>(src), src_rank_stride, slots,
+                            stamps, &state->zero, a, s)
+             : launch_once(geo, g, static_cast<const uint16_t *>(src), src_rank_stride, slots,
+                           stamps, a, s);
+    return e == hipSuccess ? SIFAR_OK : SIFAR_EHIP;
 }
