@@ -139,9 +139,10 @@ def test_epilogue_outputs_over_its_own_inputs(alias):
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
+@pytest.mark.parametrize("capture_mode", ["global", "thread_local", "relaxed"])
 @pytest.mark.parametrize("epilogue", [False, True])
 @pytest.mark.parametrize("fuse", [1, 0])
-def test_step_on_a_capturing_stream_is_not_recorded(fuse, epilogue):
+def test_step_on_a_capturing_stream_is_not_recorded(fuse, epilogue, capture_mode):
     """On a capturing stream a per-epoch step runs at once, whichever kernels
     would otherwise run it, and the host's epochs stay the device's: replays of
     the (empty) capture change nothing and the next steps go on."""
@@ -166,7 +167,7 @@ def test_step_on_a_capturing_stream_is_not_recorded(fuse, epilogue):
     side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):
-        graph.capture_begin(capture_error_mode="relaxed")
+        graph.capture_begin(capture_error_mode=capture_mode)
         try:
             epochs = run.step(3)
         finally:
